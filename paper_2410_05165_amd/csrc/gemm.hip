@@ -20,9 +20,7 @@
 //   STORE fp32 logits.
 // M is read from device memory; the grid covers the caller's row count or
 // bound (GemmCall::Mmax), and tiles past M exit at once.
-//
-// fp32 path (fp32 workloads): plain LDS-tiled FMA GEMM to a scratch matrix,
-// then an elementwise epilogue kernel with the same semantics.
+// fp32 models take the kernels of gemm_f32.hip.
 #include "common.h"
 #include "kernels.h"
 
@@ -40,9 +38,7 @@ struct EpiArgs {
   bf16_t* q;         // [M, d]
   bf16_t* kdst;      // prefix cache or tree KV base of this layer
   bf16_t* vdst;
-  const float* cosT; // fp32 path: [max_pos, dh/2]
-  const float* sinT;
-  const float* ropeT; // bf16 path: [max_pos][16][4] (cos, sin), rotary index 16*b + i at [pos][i][b]
+  const float* ropeT; // [max_pos][16][4] (cos, sin), rotary index 16*b + i at [pos][i][b]
   Rows rows;
   int kv_mode;       // 0 prefix cache [B][H][Pmax][dh], 1 tree [slot][d]
   int Pmax;
@@ -540,96 +536,6 @@ gemm_bf16_kernel(const bf16_t* __restrict__ A, int lda, const int* __restrict__ 
   }
 }
 
-// ------------------------------------------------------------------ fp32 path
-template <int BMAP>
-__global__ void __launch_bounds__(256)
-gemm_f32_kernel(const float* __restrict__ A, int lda, const int* __restrict__ Mdev, int N, int K,
-                const float* w0, const float* w1, const float* w2, int split, float* __restrict__ C) {
-  __shared__ float As[16][65];
-  __shared__ float Bs[16][65];
-  const int M = *Mdev;
-  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-  if (m0 >= M) return;
-  const int tid = threadIdx.x, tr = tid / 16, tc = tid % 16;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    for (int i = tid; i < 64 * 16; i += 256) {
-      int r = i / 16, k = i % 16;
-      int gr = m0 + r < M ? m0 + r : M - 1;
-      As[k][r] = A[(size_t)gr * lda + k0 + k];
-      int gn = n0 + r < N ? n0 + r : N - 1;
-      const float* w;
-      if (BMAP == BMAP_PLAIN) w = w0 + (size_t)gn * K;
-      else if (BMAP == BMAP_QKV) {
-        int which = gn / split;
-        w = (which == 0 ? w0 : which == 1 ? w1 : w2) + (size_t)(gn - which * split) * K;
-      } else {
-        w = (gn < split ? w0 + (size_t)gn * K : w1 + (size_t)(gn - split) * K);
-      }
-      Bs[k][r] = w[k0 + k];
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      float a[4], bb[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = As[k][tr + 16 * i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bb[j] = Bs[k][tc + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += a[i] * bb[j];
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int r = m0 + tr + 16 * i, c = n0 + tc + 16 * j;
-      if (r < M && c < N) C[(size_t)r * N + c] = acc[i][j];
-    }
-}
-
-// Elementwise epilogues of the fp32 path (C is [M, N] fp32).
-__global__ void epi_f32_kernel(const float* __restrict__ C, const int* __restrict__ Mdev, int N, int epi,
-                               EpiArgs e, int f) {
-  const int M = *Mdev;
-  const size_t total = (size_t)M * (epi == EPI_GU ? f : N);
-  for (size_t idx = blockIdx.x * (size_t)blockDim.x + threadIdx.x; idx < total; idx += (size_t)gridDim.x * blockDim.x) {
-    if (epi == EPI_RESID) {
-      e.out[idx] += C[idx];
-    } else if (epi == EPI_GU) {
-      size_t row = idx / f, c = idx % f;
-      float g = C[row * N + c], u = C[row * N + f + c];
-      reinterpret_cast<float*>(e.hout)[idx] = silu(g) * u;
-    } else if (epi == EPI_QKV) {
-      int row = (int)(idx / N), col = (int)(idx % N);
-      int which = col / e.d, hc = col - which * e.d, head = hc / e.dh, ii = hc - head * e.dh;
-      int halfdh = e.dh >> 1, pos = e.rows.pos[row];
-      float v = C[idx];
-      if (which < 2) {
-        int pc = ii < halfdh ? col + halfdh : col - halfdh;
-        float pv = C[(size_t)row * N + pc];
-        int fi = ii % halfdh;
-        float c = e.cosT[pos * halfdh + fi], s = e.sinT[pos * halfdh + fi];
-        v = ii < halfdh ? v * c - pv * s : v * c + pv * s;
-      }
-      if (which == 0) {
-        reinterpret_cast<float*>(e.q)[(size_t)row * e.d + hc] = v;
-      } else {
-        size_t kvoff = e.kv_mode == 0 ? ((size_t)e.rows.user[row] * e.H * e.Pmax + pos) * e.dh
-                                      : (size_t)e.rows.slot[row] * e.d;
-        size_t hs = e.kv_mode == 0 ? (size_t)e.Pmax * e.dh : (size_t)e.dh;
-        reinterpret_cast<float*>(which == 1 ? e.kdst : e.vdst)[kvoff + head * hs + ii] = v;
-      }
-    } else {
-      e.out[idx] = C[idx];
-    }
-  }
-}
-
 // ------------------------------------------------------------------ launchers
 // Launch of one instantiation over the tiles of a call.  The widest tiles,
 // 256x256 of 8 waves (64x128 each, two waves per SIMD), let one wave's LDS and
@@ -642,7 +548,7 @@ static hipError_t launch_bf16(const GemmCall& g, hipStream_t st) {
   e.out = g.out; e.ldo = g.ldo; e.hout = (bf16_t*)g.hout;
   e.part = EPI == EPI_RESID ? g.part : nullptr;
   e.q = (bf16_t*)g.q; e.kdst = (bf16_t*)g.kdst; e.vdst = (bf16_t*)g.vdst;
-  e.cosT = g.cosT; e.sinT = g.sinT; e.ropeT = g.ropeT; e.rows = g.rows; e.kv_mode = g.kv_mode; e.Pmax = g.Pmax;
+  e.ropeT = g.ropeT; e.rows = g.rows; e.kv_mode = g.kv_mode; e.Pmax = g.Pmax;
   e.d = g.d; e.dh = g.dh; e.H = g.H;
   const int kparts = e.part ? 2 : 1;
   // each k-range is an even number of k-tiles of 64 (two stages)
@@ -801,31 +707,7 @@ hipError_t gemm(const GemmCall& g, hipStream_t st) {
         }
     }
   }
-  // fp32: raw product into g.scratch (or straight into the logits), then the
-  // elementwise epilogue
-  dim3 grid((g.N + 63) / 64, (g.Mmax + 63) / 64);
-  const float* A = (const float*)g.A;
-  float* C = g.kind == GEMM_STORE ? g.out : g.scratch;
-  int bmap = g.kind == GEMM_QKV ? BMAP_QKV : g.kind == GEMM_GU ? BMAP_GU : BMAP_PLAIN;
-  if (bmap == BMAP_QKV)
-    hipLaunchKernelGGL(gemm_f32_kernel<BMAP_QKV>, grid, dim3(256), 0, st, A, g.lda, g.Mdev, g.N, g.K,
-                       (const float*)g.w0, (const float*)g.w1, (const float*)g.w2, g.split, C);
-  else if (bmap == BMAP_GU)
-    hipLaunchKernelGGL(gemm_f32_kernel<BMAP_GU>, grid, dim3(256), 0, st, A, g.lda, g.Mdev, g.N, g.K,
-                       (const float*)g.w0, (const float*)g.w1, nullptr, g.split, C);
-  else
-    hipLaunchKernelGGL(gemm_f32_kernel<BMAP_PLAIN>, grid, dim3(256), 0, st, A, g.lda, g.Mdev, g.N, g.K,
-                       (const float*)g.w0, nullptr, nullptr, g.split, C);
-  hipError_t err = hipGetLastError();
-  if (err != hipSuccess || g.kind == GEMM_STORE) return err;
-  EpiArgs e{};
-  e.out = g.out; e.ldo = g.ldo; e.hout = (bf16_t*)g.hout;
-  e.q = (bf16_t*)g.q; e.kdst = (bf16_t*)g.kdst; e.vdst = (bf16_t*)g.vdst;
-  e.cosT = g.cosT; e.sinT = g.sinT; e.rows = g.rows; e.kv_mode = g.kv_mode; e.Pmax = g.Pmax;
-  e.d = g.d; e.dh = g.dh; e.H = g.H;
-  int epi = g.kind == GEMM_QKV ? EPI_QKV : g.kind == GEMM_GU ? EPI_GU : g.kind == GEMM_RESID ? EPI_RESID : EPI_STORE;
-  hipLaunchKernelGGL(epi_f32_kernel, dim3(1024), dim3(256), 0, st, g.scratch, g.Mdev, g.N, epi, e, g.split);
-  return hipGetLastError();
+  return gemm_f32(g, st);
 }
 
 }  // namespace atspeed

@@ -24,9 +24,9 @@ struct GemmCall {
   const float* ropeT;        // bf16 path: [max_pos][16][4] (cos, sin) of rotary index 16*b + i at [pos][i][b] (0 past d_head/2)
   Rows rows;
   int kv_mode, Pmax, d, dh, H;
-  float* scratch;            // fp32 path: [Mmax, N] product
 };
 hipError_t gemm(const GemmCall& g, hipStream_t st);
+hipError_t gemm_f32(const GemmCall& g, hipStream_t st);   // fp32 models
 
 // Attention of every row over its visible prefix-cache keys and tree keys.
 struct AttnCall {

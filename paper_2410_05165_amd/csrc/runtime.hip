@@ -102,7 +102,6 @@ struct atspeed_ctx {
   void* ao = nullptr;
   void* h = nullptr;
   float* logits = nullptr;
-  float* scratch = nullptr;
   float* part = nullptr;      // bf16: second k-half of the o / down product [Mmax, d] fp32
   int* lo = nullptr;
   int* hi = nullptr;
@@ -375,7 +374,6 @@ void layout(atspeed_ctx& c, const atspeed_config& cfg, int trie_nodes, Arena& a)
   c.ao = a.take<char>(M * dmax * es);
   c.h = a.take<char>(M * fmax * es);
   c.logits = a.take<float>(M * c.nitem);
-  c.scratch = c.bf16 ? nullptr : a.take<float>(M * std::max(3 * dmax, 2 * fmax));
   c.part = c.bf16 ? a.take<float>(M * dmax) : nullptr;
   c.rows.M = a.take<int>(1);
   c.rows.user = a.take<int>(M);
@@ -541,7 +539,7 @@ atspeed_status forward(atspeed_ctx& c, ModelRt& r, bool prefill, int Mmax, int T
     if (cap_act) HIP_TRY(capture_act(l, 0, c.xn, d));
     GemmCall g{};
     g.bf16 = c.bf16;
-    g.Mmax = Mmax; g.Mdev = c.rows.M; g.scratch = c.scratch; g.rows = c.rows;
+    g.Mmax = Mmax; g.Mdev = c.rows.M; g.rows = c.rows;
     g.cosT = r.cosT; g.sinT = r.sinT; g.ropeT = r.ropeT; g.d = d; g.dh = dh; g.H = H; g.Pmax = c.cfg.max_prefix;
     // q, k, v (+ rotary), k/v to their cache
     g.kind = GEMM_QKV; g.A = c.xn; g.lda = d; g.N = 3 * d; g.K = d;
@@ -601,7 +599,7 @@ atspeed_status forward(atspeed_ctx& c, ModelRt& r, bool prefill, int Mmax, int T
   if (cap) { c.cap_x = nullptr; c.cap_act = nullptr; c.cap_plan = nullptr; c.cap_rows = 0; }
   GemmCall g{};
   g.kind = GEMM_STORE; g.bf16 = c.bf16; g.A = c.xn; g.lda = d; g.Mmax = Mmf; g.Mdev = Mfin;
-  g.N = c.nitem; g.K = d; g.w0 = r.lm_head; g.out = c.logits; g.ldo = c.nitem; g.scratch = c.scratch;
+  g.N = c.nitem; g.K = d; g.w0 = r.lm_head; g.out = c.logits; g.ldo = c.nitem;
   MARK_F(ATSPEED_K_LMHEAD, 2.0 * Mmf * c.nitem * d);
   HIP_TRY(gemm(g, st));
   MARK(ATSPEED_K_ROW);
@@ -1204,7 +1202,7 @@ atspeed_status atspeed_align_step(atspeed_ctx* c, const atspeed_align_args* a, d
   {
     GemmCall g{};
     g.kind = GEMM_STORE; g.bf16 = c->bf16; g.A = c->root_h; g.lda = d; g.Mmax = B; g.Mdev = c->Mb;
-    g.N = c->nitem; g.K = d; g.w0 = r.lm_head; g.out = c->logits; g.ldo = c->nitem; g.scratch = c->scratch;
+    g.N = c->nitem; g.K = d; g.w0 = r.lm_head; g.out = c->logits; g.ldo = c->nitem;
     HIP_TRY(gemm(g, c->st));
     HIP_TRY(log_softmax_rows(c->logits, c->Mb, B, c->nitem, nullptr, r.root, nullptr, c->st));
   }

@@ -1,0 +1,44 @@
+"""fp32 models at the edges of the fp32 projections' tiles: d_ffn an odd multiple
+of 16 (the last k-tile of the down projection is half filled, the last gate/up
+column group stands alone), an item head of a width that is no multiple of a
+tile, every d_head, row counts below, at and past a tile, and the three tile
+sizes, against the fp64 oracle."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+from oracle.model import Decoder  # noqa: E402
+from synth import ModelDims, get_workload, make_catalog, make_prefixes, make_weights  # noqa: E402
+
+CASES = {
+    # name: (d_model, heads, d_ffn, codebook, users, history items)
+    "dh32_half_tail": (96, 3, 16 * 21, 50, 1, 4),          # 16 rows, K 336 = 10.5 k-tiles
+    "dh64_one_row_over": (128, 2, 16, 33, 1, 16),          # d_ffn 16: half a k-tile; 64 rows, then trees
+    "dh128_ragged_rows": (256, 2, 16 * 5, 255, 3, 11),     # 132 rows, 1,020 head columns
+    "mid_tiles": (512, 8, 1408, 256, 9, 17),               # 64x64 tiles, 612 rows
+    "large_tiles": (1024, 8, 2816, 256, 12, 33),           # 128x128 tiles, 1,584 rows
+}
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_fp32_prefill_logits(name):
+    from paper_2410_05165_amd.binding import Engine
+    d, heads, ffn, codebook, users, hist = CASES[name]
+    dims = ModelDims(1, d, heads, ffn, 4 * codebook + 8, 8)
+    w = get_workload("tiny").with_(name=name, target=dims, draft=ModelDims(0, 0, 0, 0, 0, 0), codebook=codebook,
+                                   n_items=400, batch=users, hist_items=hist, prompt_len=0)
+    cat = make_catalog(w)
+    pre = make_prefixes(w, cat)
+    tw = make_weights(w, "target")
+    eng = Engine(w, tw, None, cat)
+    root = torch.full((users, w.n_item_tokens), float("nan"), dtype=torch.float32, device="cuda:0")
+    eng.atspeed_prefill(torch.from_numpy(pre).cuda(), root)
+    torch.cuda.synchronize()
+    got = root.cpu().numpy()
+    dec = Decoder(dims, tw, "fp32")
+    for u in range(users):
+        np.testing.assert_allclose(got[u], dec.prefill(pre[u]).last_logits, rtol=0, atol=1e-4)
+    eng.close()
