@@ -7,204 +7,202 @@
 // prefix K/V are streamed once per workgroup in 64-key tiles through LDS and
 // shared by all its queries (the prefix is read once per user per layer, not
 // once per tree token).  Softmax is online (running max and sum) in fp32.
+// Workgroup L runs on XCD L % 8: the (user, head) pairs are dealt round-robin
+// over the XCDs, a pair's query blocks on one of them.
 #include "common.h"
 #include "kernels.h"
 
 namespace atspeed {
 
-constexpr int AQ = 64;  // query rows per workgroup
-constexpr int AK = 64;  // keys per tile
-
-template <class T, int DH>
+// ---------------------------------------------------------------- fp32 kernel
+// Per workgroup: (head, user, 64 query rows); wave w owns queries 16w..16w+15.
+// S^T = K Q^T with v_mfma_f32_16x16x4_f32, a lane's 16-byte K and Q fragments
+// feeding four of them (MFMA e takes dims 16 ks + 4 (lane / 16) + e).  Lane l
+// then holds S^T[key 4g+i][query l%16] (g = l/16), which is the B operand of
+// O^T = V^T P^T for the MFMA over keys {i, 4+i, 8+i, 12+i}, so probabilities stay
+// in registers.  Each query's tree keys (ancestors and itself) follow, one dot
+// product split over the 4 lanes of the query.
+//
+// Bound by latency at the sizes fp32 models run (tens of rows, a few key tiles):
+// the next tile's loads are in flight during the current tile's MFMAs, and the
+// key range is the last row's, so nothing is exchanged before the first tile.
+// One user's 30-60 rows over 80 keys at d_head 32 took 18-21 us with vector FMAs
+// over LDS and take 7-9; 120 rows x 8 users over 120 keys at d_head 64, 41 -> 15.
+template <int DH>
 __global__ void __launch_bounds__(256)
-attn_kernel(const T* __restrict__ q, const T* __restrict__ pk, const T* __restrict__ pv,
-            const T* __restrict__ tk, const T* __restrict__ tv, T* __restrict__ out, Rows rows,
-            int H, int Pmax, float qscale) {
-  constexpr int DP = DH + 1;
-  constexpr int OD = DH / 16;  // output dims per thread
-  extern __shared__ __align__(16) float sm[];
-  float* Qs = sm;                  // [AQ][DP]
-  float* Ks = Qs + AQ * DP;        // [AK][DP]
-  float* Vs = Ks + AK * DP;        // [AK][DH]
-  float* Ss = Vs + AK * DH;        // [AQ][AK + 1]
-  __shared__ float m_s[AQ], l_s[AQ], a_s[AQ];
-  __shared__ int nctx_s[AQ], anc_s[AQ][4], nanc_s[AQ];
-  __shared__ int kmax_s;
+attn_f32_kernel(const float* __restrict__ q, const float* __restrict__ pk, const float* __restrict__ pv,
+                const float* __restrict__ tk, const float* __restrict__ tv, float* __restrict__ out, Rows rows,
+                int H, int Pmax, float qscale, int nusers, int nqblk) {
+  constexpr int KT = 64;          // keys per tile
+  constexpr int NKS = DH / 16;    // 16-dim groups of S^T
+  constexpr int NDB = DH / 16;    // 16-dim blocks of O^T
+  constexpr int CPR = DH / 4;     // 16-byte chunks per row
+  __shared__ __align__(16) float Ks[KT * DH];
+  __shared__ __align__(16) float Vs[KT * DH];
+  // chunk swizzles: K fragments are read 16 rows at one chunk, V 4 rows (4 apart)
+  // at one 16-dim block
+  auto kswz = [](int key) { return CPR >= 16 ? key & 15 : (key >> 1) & 7; };
+  auto vswz = [](int key) { return ((key >> 2) & (NDB >= 4 ? 3 : 1)) << 2; };
 
-  const int u = blockIdx.y, h = blockIdx.x;
+  const int Lw = blockIdx.x, xcd = Lw & 7, qi8 = Lw >> 3, Z = nqblk;
+  const int pair = (qi8 / Z) * 8 + xcd, zb = qi8 % Z;
+  if (pair >= H * nusers) return;
+  const int u = pair / H, h = pair % H;
   const int ubeg = rows.user_off[u], uend = rows.user_off[u + 1];
-  const int r0 = ubeg + blockIdx.z * AQ;
+  const int r0 = ubeg + zb * 64;
   if (r0 >= uend) return;
-  const int nq = min(AQ, uend - r0);
-  const int tid = threadIdx.x;
+  const int nq = min(64, uend - r0);
+  const int kmax = rows.nctx[r0 + nq - 1];   // never decreases along a user's rows
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int g = lane >> 4, ql = lane & 15;
+  const int qi = wave * 16 + ql;
+  const bool valid = qi < nq;
+  const int row = r0 + (valid ? qi : 0);
   const int d = H * DH;
-
-  if (tid == 0) kmax_s = 0;
-  __syncthreads();
-  if (tid < AQ) {
-    int n = 0;
-    if (tid < nq) {
-      n = rows.nctx[r0 + tid];
-      nanc_s[tid] = rows.nanc[r0 + tid];
-      for (int a = 0; a < 4; ++a) anc_s[tid][a] = rows.anc[(r0 + tid) * 4 + a];
-    } else {
-      nanc_s[tid] = 0;
-    }
-    nctx_s[tid] = n;
-    m_s[tid] = -INFINITY;
-    l_s[tid] = 0.f;
-    atomicMax(&kmax_s, n);
-  }
-  for (int i = tid; i < AQ * DH; i += 256) {
-    int r = i / DH, c = i % DH;
-    Qs[r * DP + c] = r < nq ? St<T>::ld(q + (size_t)(r0 + r) * d + h * DH + c) * qscale : 0.f;
-  }
-  __syncthreads();
-  const int kmax = kmax_s;
-
-  const int tq = tid >> 4, tkk = tid & 15;   // S tile: 4 queries x 4 keys per thread
-  const int oq = tid >> 4, od = tid & 15;    // O tile: 4 queries x OD dims per thread
-  float o[4][OD];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < OD; ++j) o[i][j] = 0.f;
-
   const size_t kvbase = ((size_t)u * H + h) * Pmax * DH;
-  for (int k0 = 0; k0 < kmax; k0 += AK) {
-    const int nk = min(AK, kmax - k0);
-    for (int i = tid; i < AK * DH; i += 256) {
-      int r = i / DH, c = i % DH;
-      float kv = 0.f, vv = 0.f;
-      if (r < nk) {
-        kv = St<T>::ld(pk + kvbase + (size_t)(k0 + r) * DH + c);
-        vv = St<T>::ld(pv + kvbase + (size_t)(k0 + r) * DH + c);
-      }
-      Ks[r * DP + c] = kv;
-      Vs[r * DH + c] = vv;
+
+  constexpr int NC = KT * CPR / 256;         // chunks per thread of a K (or V) tile
+  f32x4_t kreg[NC], vreg[NC];
+  auto fetch = [&](int k0) {
+    const int nk = min(KT, kmax - k0);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int idx = tid + c * 256, key = idx / CPR, j = idx % CPR;
+      const size_t o = kvbase + (size_t)(k0 + key) * DH + j * 4;
+      kreg[c] = key < nk ? *reinterpret_cast<const f32x4_t*>(pk + o) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+      vreg[c] = key < nk ? *reinterpret_cast<const f32x4_t*>(pv + o) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+  };
+  if (kmax > 0) fetch(0);
+  const int nctx = valid ? rows.nctx[row] : 0;
+  f32x4_t qf[NKS];
+#pragma unroll
+  for (int ks = 0; ks < NKS; ++ks)
+    qf[ks] = valid ? *reinterpret_cast<const f32x4_t*>(q + (size_t)row * d + h * DH + ks * 16 + g * 4)
+                   : f32x4_t{0.f, 0.f, 0.f, 0.f};
+  f32x4_t o[NDB];
+#pragma unroll
+  for (int i = 0; i < NDB; ++i) o[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY, lsum = 0.f;
+
+  for (int k0 = 0; k0 < kmax; k0 += KT) {
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int idx = tid + c * 256, key = idx / CPR, j = idx % CPR;
+      *reinterpret_cast<f32x4_t*>(Ks + key * DH + (j ^ kswz(key)) * 4) = kreg[c];
+      *reinterpret_cast<f32x4_t*>(Vs + key * DH + (j ^ vswz(key)) * 4) = vreg[c];
     }
     __syncthreads();
-    float s[4][4];
+    if (k0 + KT < kmax) fetch(k0 + KT);
+    f32x4_t sc[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int kb = 0; kb < 4; ++kb) sc[kb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int j = 0; j < 4; ++j) s[i][j] = 0.f;
-    for (int c = 0; c < DH; ++c) {
-      float qa[4], ka[4];
+    for (int ks = 0; ks < NKS; ++ks) {
+      f32x4_t kf[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) qa[i] = Qs[(tq * 4 + i) * DP + c];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) ka[j] = Ks[(tkk + 16 * j) * DP + c];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) s[i][j] += qa[i] * ka[j];
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        int qi = tq * 4 + i, kj = tkk + 16 * j;
-        Ss[qi * (AK + 1) + kj] = (k0 + kj < nctx_s[qi]) ? s[i][j] : -INFINITY;
+      for (int kb = 0; kb < 4; ++kb) {
+        const int key = kb * 16 + ql;
+        kf[kb] = *reinterpret_cast<const f32x4_t*>(Ks + key * DH + ((ks * 4 + g) ^ kswz(key)) * 4);
       }
-    __syncthreads();
-    {  // online softmax: 4 threads per query row, 16 keys each
-      const int row = tid >> 2, part = tid & 3;
-      float mx = -INFINITY;
-      for (int j = 0; j < 16; ++j) mx = fmaxf(mx, Ss[row * (AK + 1) + part * 16 + j]);
-      mx = fmaxf(mx, __shfl_xor(mx, 1));
-      mx = fmaxf(mx, __shfl_xor(mx, 2));
-      const float mold = m_s[row];
-      const float mnew = fmaxf(mold, mx);
-      float sum = 0.f;
-      for (int j = 0; j < 16; ++j) {
-        float sv = Ss[row * (AK + 1) + part * 16 + j];
-        float p = (sv == -INFINITY) ? 0.f : exp2f(sv - mnew);
-        Ss[row * (AK + 1) + part * 16 + j] = p;
-        sum += p;
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int kb = 0; kb < 4; ++kb)
+          sc[kb] = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[kb][e], qf[ks][e], sc[kb], 0, 0, 0);
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int key = k0 + kb * 16 + g * 4 + i;
+        const float v = key < nctx ? sc[kb][i] * qscale : -INFINITY;
+        sc[kb][i] = v;
+        mx = fmaxf(mx, v);
       }
-      sum += __shfl_xor(sum, 1);
-      sum += __shfl_xor(sum, 2);
-      __syncthreads();  // every lane has read m_s[row] before it changes
-      if (part == 0) {
-        const float alpha = (mold == -INFINITY) ? 0.f : exp2f(mold - mnew);
-        a_s[row] = alpha;
-        l_s[row] = l_s[row] * alpha + sum;
-        m_s[row] = mnew;
+    mx = fmaxf(mx, __shfl_xor(mx, 16));
+    mx = fmaxf(mx, __shfl_xor(mx, 32));
+    const float mnew = fmaxf(m, mx);
+    const float alpha = (m == -INFINITY) ? 0.f : exp2f(m - mnew);
+    float ps = 0.f;
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float p = (sc[kb][i] == -INFINITY) ? 0.f : exp2f(sc[kb][i] - mnew);
+        sc[kb][i] = p;
+        ps += p;
       }
-    }
-    __syncthreads();
+    lsum = lsum * alpha + ps;
+    m = mnew;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float al = a_s[oq * 4 + i];
+    for (int db = 0; db < NDB; ++db) o[db] *= alpha;
 #pragma unroll
-      for (int j = 0; j < OD; ++j) o[i][j] *= al;
-    }
-    for (int kj = 0; kj < nk; ++kj) {
-      float pa[4], va[OD];
+    for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) pa[i] = Ss[(oq * 4 + i) * (AK + 1) + kj];
+      for (int i = 0; i < 4; ++i) {
+        const int key = kb * 16 + 4 * g + i;
 #pragma unroll
-      for (int j = 0; j < OD; ++j) va[j] = Vs[kj * DH + od + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < OD; ++j) o[i][j] += pa[i] * va[j];
-    }
+        for (int db = 0; db < NDB; ++db) {
+          const int dim = db * 16 + ql;
+          const float vf = Vs[key * DH + (((dim >> 2) ^ vswz(key)) << 2) + (dim & 3)];
+          o[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf, sc[kb][i], o[db], 0, 0, 0);
+        }
+      }
     __syncthreads();
   }
 
-  if (tk != nullptr) {  // tree keys: ancestors and self of every query
-    {
-      const int row = tid >> 2, a = tid & 3;
-      float sv = -INFINITY;
-      if (a < nanc_s[row]) {
-        const T* kp = tk + (size_t)anc_s[row][a] * d + h * DH;
-        float acc = 0.f;
-        for (int c = 0; c < DH; ++c) acc += Qs[row * DP + c] * St<T>::ld(kp + c);
-        sv = acc;
+  if (tk != nullptr && valid) {  // tree keys: ancestors and self
+    const int na = rows.nanc[row];
+    int slot[4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) slot[a] = a < na ? rows.anc[row * 4 + a] : 0;
+    float sa[4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) {
+      float part = 0.f;
+      if (a < na) {
+        const float* kp = tk + (size_t)slot[a] * d + h * DH + g * 4;
+#pragma unroll
+        for (int ks = 0; ks < NKS; ++ks) {
+          const f32x4_t kf = *reinterpret_cast<const f32x4_t*>(kp + ks * 16);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) part += qf[ks][e] * kf[e];
+        }
       }
-      float mx = sv;
-      mx = fmaxf(mx, __shfl_xor(mx, 1));
-      mx = fmaxf(mx, __shfl_xor(mx, 2));
-      const float mold = m_s[row];
-      const float mnew = fmaxf(mold, mx);
-      const float p = (sv == -INFINITY) ? 0.f : exp2f(sv - mnew);
-      Ss[row * (AK + 1) + a] = p;
-      float sum = p;
-      sum += __shfl_xor(sum, 1);
-      sum += __shfl_xor(sum, 2);
-      __syncthreads();
-      if (a == 0) {
-        const float alpha = (mold == -INFINITY) ? 0.f : exp2f(mold - mnew);
-        a_s[row] = alpha;
-        l_s[row] = l_s[row] * alpha + sum;
-        m_s[row] = mnew;
-      }
+      part += __shfl_xor(part, 16);
+      part += __shfl_xor(part, 32);
+      sa[a] = a < na ? part * qscale : -INFINITY;
     }
-    __syncthreads();
+    const float mx = fmaxf(fmaxf(sa[0], sa[1]), fmaxf(sa[2], sa[3]));
+    const float mnew = fmaxf(m, mx);
+    const float alpha = (m == -INFINITY) ? 0.f : exp2f(m - mnew);
+    float ps = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int qi = oq * 4 + i;
-      const float al = a_s[qi];
-#pragma unroll
-      for (int j = 0; j < OD; ++j) o[i][j] *= al;
-      for (int a = 0; a < nanc_s[qi]; ++a) {
-        const float p = Ss[qi * (AK + 1) + a];
-        const T* vp = tv + (size_t)anc_s[qi][a] * d + h * DH;
-#pragma unroll
-        for (int j = 0; j < OD; ++j) o[i][j] += p * St<T>::ld(vp + od + 16 * j);
-      }
+    for (int a = 0; a < 4; ++a) {
+      sa[a] = a < na ? exp2f(sa[a] - mnew) : 0.f;
+      ps += sa[a];
     }
+    lsum = lsum * alpha + (g == 0 ? ps : 0.f);
+    // lane (query, g) holds dims db*16 + 4g .. +3 of O
+#pragma unroll
+    for (int db = 0; db < NDB; ++db) o[db] *= alpha;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+      if (a < na) {
+        const float* vp = tv + (size_t)slot[a] * d + h * DH + g * 4;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db) o[db] += sa[a] * *reinterpret_cast<const f32x4_t*>(vp + db * 16);
+      }
   }
-  __syncthreads();
+  lsum += __shfl_xor(lsum, 16);
+  lsum += __shfl_xor(lsum, 32);
+  if (valid) {
+    const float inv = 1.f / lsum;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int qi = oq * 4 + i;
-    if (qi >= nq) continue;
-    const float inv = 1.f / l_s[qi];
-#pragma unroll
-    for (int j = 0; j < OD; ++j) St<T>::st(out + (size_t)(r0 + qi) * d + h * DH + od + 16 * j, o[i][j] * inv);
+    for (int db = 0; db < NDB; ++db)
+      *reinterpret_cast<f32x4_t*>(out + (size_t)row * d + h * DH + db * 16 + g * 4) = o[db] * inv;
   }
 }
 
@@ -449,44 +447,27 @@ attn_mfma_kernel(const bf16_t* __restrict__ q, const bf16_t* __restrict__ pk, co
   }
 }
 
-template <int DH>
-static hipError_t launch_attn_mfma(const AttnCall& a, hipStream_t st) {
-  const float qscale = 1.4426950408889634f / sqrtf((float)DH);
-  // one-dimensional grid: ceil(pairs / 8) groups of 8 pairs x Z query blocks
+// One-dimensional grid: ceil(pairs / 8) groups of 8 (user, head) pairs x Z query blocks.
+template <class T, class F>
+static hipError_t launch(const AttnCall& a, F kern, int dh, hipStream_t st) {
+  const float qscale = 1.4426950408889634f / sqrtf((float)dh);   // log2(e) / sqrt(d_head)
   const int Z = std::max(1, (a.Tq + 63) / 64);
   const long pairs = (long)a.H * a.B;
   const long nwg = (pairs + 7) / 8 * 8 * Z;
   if (nwg > 0x7fffffffL) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(attn_mfma_kernel<DH>, dim3((unsigned)nwg), dim3(256), 0, st, (const bf16_t*)a.q,
-                     (const bf16_t*)a.pk, (const bf16_t*)a.pv, (const bf16_t*)a.tk, (const bf16_t*)a.tv,
-                     (bf16_t*)a.out, a.rows, a.H, a.Pmax, qscale, a.B, Z);
-  return hipGetLastError();
-}
-
-template <class T, int DH>
-static hipError_t launch_attn(const AttnCall& a, hipStream_t st) {
-  constexpr int DP = DH + 1;
-  const size_t smem = sizeof(float) * (AQ * DP + AK * DP + AK * DH + AQ * (AK + 1));
-  auto kern = attn_kernel<T, DH>;
-  // set on every launch: the attribute is per device, and this path (fp32
-  // workloads) is not the one whose launch cost matters
-  hipError_t err = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-  if (err != hipSuccess) return err;
-  const float qscale = 1.4426950408889634f / sqrtf((float)DH);  // log2(e) / sqrt(d_head)
-  dim3 grid(a.H, a.B, (a.Tq + AQ - 1) / AQ);  // query blocks slowest, as in the MFMA kernel
-  hipLaunchKernelGGL(kern, grid, dim3(256), smem, st, (const T*)a.q, (const T*)a.pk, (const T*)a.pv,
-                     (const T*)a.tk, (const T*)a.tv, (T*)a.out, a.rows, a.H, a.Pmax, qscale);
+  hipLaunchKernelGGL(kern, dim3((unsigned)nwg), dim3(256), 0, st, (const T*)a.q, (const T*)a.pk, (const T*)a.pv,
+                     (const T*)a.tk, (const T*)a.tv, (T*)a.out, a.rows, a.H, a.Pmax, qscale, a.B, Z);
   return hipGetLastError();
 }
 
 hipError_t attention(const AttnCall& a, hipStream_t st) {
   if (a.bf16) {
-    if (a.dh == 64) return launch_attn_mfma<64>(a, st);
-    if (a.dh == 128) return launch_attn_mfma<128>(a, st);
+    if (a.dh == 64) return launch<bf16_t>(a, attn_mfma_kernel<64>, 64, st);
+    if (a.dh == 128) return launch<bf16_t>(a, attn_mfma_kernel<128>, 128, st);
   } else {
-    if (a.dh == 64) return launch_attn<float, 64>(a, st);
-    if (a.dh == 128) return launch_attn<float, 128>(a, st);
-    if (a.dh == 32) return launch_attn<float, 32>(a, st);
+    if (a.dh == 32) return launch<float>(a, attn_f32_kernel<32>, 32, st);
+    if (a.dh == 64) return launch<float>(a, attn_f32_kernel<64>, 64, st);
+    if (a.dh == 128) return launch<float>(a, attn_f32_kernel<128>, 128, st);
   }
   return hipErrorInvalidValue;
 }

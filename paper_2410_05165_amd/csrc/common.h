@@ -58,7 +58,7 @@ struct Rows {
   int* token;        // [Mmax]
   int* pos;          // [Mmax] rotary position
   int* slot;         // [Mmax] tree slot (u*Tmax + s) or -1 for prefix rows
-  int* nctx;         // [Mmax] visible prefix-cache keys
+  int* nctx;         // [Mmax] visible prefix-cache keys (never decreasing along a user's rows)
   int* anc;          // [Mmax * 4] tree slots of ancestors-or-self, depth order
   int* nanc;         // [Mmax]
   int* user_off;     // [B + 1] first row of each user (rows of a user are contiguous)
