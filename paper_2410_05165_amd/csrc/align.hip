@@ -126,6 +126,15 @@ __global__ void align_logpk_kernel(const int* __restrict__ items, const int* __r
   log_pK[u * L + t] = row[codebook * t + code];
 }
 
+// Sum over the 256 threads of a workgroup, the same for all.
+__device__ __forceinline__ float block_sum(float v, float* part) {
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = v;
+  __syncthreads();
+  return (part[0] + part[1]) + (part[2] + part[3]);
+}
+
 // One workgroup per context row: rows [0, B) are the users' roots, row B + r is
 // row r of the draft's forward over the context tree.  dz row = alpha w dl/dz +
 // (1 - alpha)(w q - lw), lw the label weights of the context's children in the
@@ -136,7 +145,7 @@ align_grad_kernel(AlignRows ar, TrieDev trie, TreeDev tr, int B, int nitem, int 
                   float alpha, float* __restrict__ dz, float* __restrict__ loss_rows) {
   __shared__ float cq[256], cp[256], chw[256];
   __shared__ int ccol[256], sel[256];
-  __shared__ float red[4];
+  __shared__ float red[4], part[4];
   const int row = blockIdx.x, tid = threadIdx.x;
   if (row >= B + *ar.Mdev) return;
   int u, slot, node, lvl;
@@ -186,33 +195,33 @@ align_grad_kernel(AlignRows ar, TrieDev trie, TreeDev tr, int B, int nitem, int 
     sel[tid] = r < kk;
   }
   __syncthreads();
-  // sums in a fixed order (one thread)
-  if (tid == 0) {
-    float l = 0.f, sq = 0.f, sp = 0.f, sg = 0.f, rec = 0.f;
-    const float lpk = mode == 0 ? ar.log_pK[u * L + lvl] : 0.f;
+  // sums over the candidates and labels, in a fixed order (a tree over the
+  // workgroup; one thread's serial loop over up to 256 of each took 40 of the
+  // kernel's 51 us at 986 contexts)
+  {
+    const bool in = tid < n && sel[tid];
+    const float q = in ? expf(cq[tid]) : 0.f;
+    const float lab = tid < codebook ? chw[tid] : 0.f;
+    const float rec = block_sum(lab != 0.f ? -lab * lq[codebook * lvl + tid] : 0.f, part);
+    float l, second, sp = 0.f, sg = 0.f;
     if (mode == 0) {
-      for (int i = 0; i < n; ++i)
-        if (sel[i]) l += expf(cq[i]) * (lpk - cp[i]);
+      second = ar.log_pK[u * L + lvl];
+      l = block_sum(in ? q * (second - cp[tid]) : 0.f, part);
     } else {
-      for (int i = 0; i < n; ++i)
-        if (sel[i]) {
-          sq += expf(cq[i]);
-          sp += expf(cp[i]);
-        }
-      for (int i = 0; i < n; ++i)
-        if (sel[i]) {
-          const float qn = expf(cq[i]) / sq, pn = expf(cp[i]) / sp;
-          l += 0.5f * fabsf(pn - qn);
-          sg += (qn > pn ? 1.f : (qn < pn ? -1.f : 0.f)) * qn;
-        }
+      const float pe = in ? expf(cp[tid]) : 0.f;
+      second = block_sum(q, part);
+      sp = block_sum(pe, part);
+      const float qn = q / second, pn = pe / sp;
+      l = block_sum(in ? 0.5f * fabsf(pn - qn) : 0.f, part);
+      sg = block_sum(in ? (qn > pn ? 1.f : (qn < pn ? -1.f : 0.f)) * qn : 0.f, part);
     }
-    for (int c = 0; c < codebook; ++c)
-      if (chw[c] != 0.f) rec -= chw[c] * lq[codebook * lvl + c];
-    red[0] = l;
-    red[1] = mode == 0 ? lpk : sq;
-    red[2] = sp;
-    red[3] = sg;
-    loss_rows[row] = alpha * w * l + (1.f - alpha) * rec;
+    if (tid == 0) {
+      red[0] = l;
+      red[1] = second;
+      red[2] = sp;
+      red[3] = sg;
+      loss_rows[row] = alpha * w * l + (1.f - alpha) * rec;
+    }
   }
   __syncthreads();
   const float l = red[0];
@@ -237,53 +246,89 @@ align_grad_kernel(AlignRows ar, TrieDev trie, TreeDev tr, int B, int nitem, int 
   if (tid < codebook && chw[tid] != 0.f) g[codebook * lvl + tid] -= (1.f - alpha) * chw[tid];
 }
 
-// dW[v][k] = sum_rows dz[row][v] * h[row][k] in fp32; rows [0, B) take the
-// roots' hidden states, the others the context rows'.  A 64x64 output tile per
-// workgroup (4x4 per thread), rows in a fixed order, so the result does not
-// depend on the launch.
+// Eight consecutive stored values (16-byte aligned) as floats.
+__device__ __forceinline__ void load8(const float* p, float (&v)[8]) {
+  const f32x4_t a = *reinterpret_cast<const f32x4_t*>(p), b = *reinterpret_cast<const f32x4_t*>(p + 4);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { v[i] = a[i]; v[4 + i] = b[i]; }
+}
+__device__ __forceinline__ void load8(const bf16_t* p, float (&v)[8]) {
+  const u32x4_t w = *reinterpret_cast<const u32x4_t*>(p);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = __uint_as_float((i & 1) ? w[i >> 1] & 0xffff0000u : w[i >> 1] << 16);
+}
+
+// dW[v][k] = sum_rows dz[row][v] * h[row][k] in fp32 on v_mfma_f32_16x16x4_f32
+// (four rows an instruction, rows in a fixed order, so the result does not
+// depend on the launch).  A 32x64 output tile per workgroup, 16x32 per wave: the
+// gradient of 1,024 item rows at d 768 is 384 workgroups.  Bound by the latency
+// of a chunk's loads, so a chunk is 64 rows and the next one's loads are in
+// flight during its MFMAs.  64x64 tiles of vector FMAs over 32-row chunks took
+// 195 us at 986 rows of d 768, this takes 25.  LDS row strides of 48 and 80 words put the four
+// rows an instruction reads on disjoint banks.
 template <class T>
 __global__ void __launch_bounds__(256)
 head_grad_kernel(const float* __restrict__ dz, const T* __restrict__ h_root, const T* __restrict__ h_rows,
                  const int* __restrict__ Mdev, int B, int nitem, int d, float* __restrict__ dW) {
-  __shared__ float Gs[32][65];
-  __shared__ float Hs[32][65];
-  const int v0 = blockIdx.y * 64, k0 = blockIdx.x * 64, tid = threadIdx.x;
+  constexpr int RC = 64, GS = 48, HS = 80;
+  __shared__ __align__(16) float Gs[RC * GS];
+  __shared__ __align__(16) float Hs[RC * HS];
+  const int v0 = blockIdx.y * 32, k0 = blockIdx.x * 64, tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6, wv = wave >> 1, wk = wave & 1;
   const int nrows = B + *Mdev;
-  const int tv = tid / 16, tk = tid % 16;
-  float acc[4][4] = {};
-  for (int r0 = 0; r0 < nrows; r0 += 32) {
-    for (int i = tid; i < 32 * 64; i += 256) {
-      const int r = i / 64, c = i % 64, row = r0 + r;
-      float gv = 0.f, hv = 0.f;
-      if (row < nrows) {
-        if (v0 + c < nitem) gv = dz[(size_t)row * nitem + v0 + c];
-        if (k0 + c < d)
-          hv = row < B ? St<T>::ld(h_root + (size_t)row * d + k0 + c)
-                       : St<T>::ld(h_rows + (size_t)(row - B) * d + k0 + c);
+  // a thread's 8 columns of one row of dz, and of two rows of h (d_model is a
+  // multiple of 16, so a group of 8 is wholly in or out)
+  const int gr = tid >> 2, gc = (tid & 3) * 8, hr = tid >> 3, hc = (tid & 7) * 8;
+  const bool vec = (nitem & 3) == 0 && v0 + 32 <= nitem;   // rows of dz are 16-byte aligned and whole
+  float gv[8], hv[2][8];
+  auto fetch = [&](int r0) {
+    const float* g = dz + (size_t)(r0 + gr) * nitem + v0 + gc;
+    if (r0 + gr < nrows && vec) {
+      load8(g, gv);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) gv[i] = r0 + gr < nrows && v0 + gc + i < nitem ? g[i] : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int row = r0 + hr + 32 * j;
+      if (row < nrows && k0 + hc < d) {
+        load8((row < B ? h_root + (size_t)row * d : h_rows + (size_t)(row - B) * d) + k0 + hc, hv[j]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) hv[j][i] = 0.f;
       }
-      Gs[r][c] = gv;
-      Hs[r][c] = hv;
+    }
+  };
+  f32x4_t acc[2] = {f32x4_t{0.f, 0.f, 0.f, 0.f}, f32x4_t{0.f, 0.f, 0.f, 0.f}};
+  const int fr = lane & 15, kg = lane >> 4;
+  fetch(0);
+  for (int r0 = 0; r0 < nrows; r0 += RC) {
+#pragma unroll
+    for (int i = 0; i < 8; i += 4) {
+      *reinterpret_cast<f32x4_t*>(Gs + gr * GS + gc + i) = f32x4_t{gv[i], gv[i + 1], gv[i + 2], gv[i + 3]};
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        *reinterpret_cast<f32x4_t*>(Hs + (hr + 32 * j) * HS + hc + i) =
+            f32x4_t{hv[j][i], hv[j][i + 1], hv[j][i + 2], hv[j][i + 3]};
     }
     __syncthreads();
-    for (int r = 0; r < 32; ++r) {
-      float a[4], b[4];
+    if (r0 + RC < nrows) fetch(r0 + RC);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) a[i] = Gs[r][tv + 16 * i];
+    for (int s = 0; s < RC / 4; ++s) {
+      const float a = Gs[(4 * s + kg) * GS + wv * 16 + fr];
 #pragma unroll
-      for (int j = 0; j < 4; ++j) b[j] = Hs[r][tk + 16 * j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_fmaf(a[i], b[j], acc[i][j]);
+      for (int j = 0; j < 2; ++j)
+        acc[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Hs[(4 * s + kg) * HS + wk * 32 + j * 16 + fr], acc[j], 0, 0, 0);
     }
     __syncthreads();
   }
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int j = 0; j < 2; ++j)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int v = v0 + tv + 16 * i, k = k0 + tk + 16 * j;
-      if (v < nitem && k < d) dW[(size_t)v * d + k] = acc[i][j];
+    for (int r = 0; r < 4; ++r) {
+      const int v = v0 + wv * 16 + kg * 4 + r, k = k0 + wk * 32 + j * 16 + fr;
+      if (v < nitem && k < d) dW[(size_t)v * d + k] = acc[j][r];
     }
 }
 
@@ -371,7 +416,7 @@ void launch_align_grad(const AlignRows& ar, const TrieDev& trie, const TreeDev& 
 
 void launch_head_grad(bool bf16, const float* dz, const void* h_root, const void* h_rows, const int* Mdev, int B,
                       int nitem, int d, float* dW, hipStream_t st) {
-  const dim3 grid((d + 63) / 64, (nitem + 63) / 64);
+  const dim3 grid((d + 63) / 64, (nitem + 31) / 32);
   if (bf16)
     hipLaunchKernelGGL(head_grad_kernel<bf16_t>, grid, dim3(256), 0, st, dz, (const bf16_t*)h_root,
                        (const bf16_t*)h_rows, Mdev, B, nitem, d, dW);

@@ -20,14 +20,33 @@ __device__ __forceinline__ float key_score(uint64_t key) {
   return __uint_as_float(u);
 }
 
+// Child of `node` with this code, or -1.  A node's children have distinct
+// ascending codes below 256, so child i has a code of at least i and at most
+// 256 - cnt + i, which bounds where the code can sit; what is left is narrowed
+// eightfold a round by loads that do not wait for each other (a binary search's
+// eight dependent loads per level made a tree walk's latency).
 __device__ inline int trie_child(const TrieDev& t, int node, int code) {
-  int lo = t.first[node], hi = lo + t.cnt[node] - 1;
-  while (lo <= hi) {
-    int mid = (lo + hi) >> 1, c = t.code[mid];
-    if (c == code) return mid;
-    if (c < code) lo = mid + 1; else hi = mid - 1;
+  const int first = t.first[node], cnt = t.cnt[node];
+  const int* c = t.code + first;
+  int lo = max(0, code - (256 - cnt)), hi = min(cnt - 1, code);
+  while (hi - lo > 7) {
+    const int step = (hi - lo + 8) >> 3;      // at least 2; eight runs cover lo .. hi
+    int n = 0;
+#pragma unroll
+    for (int k = 1; k < 8; ++k) {
+      const int p = lo + k * step;
+      n += p <= hi && c[min(p, hi)] <= code;
+    }
+    lo += n * step;
+    hi = min(hi, lo + step - 1);
   }
-  return -1;
+  int found = -1;
+#pragma unroll
+  for (int k = 0; k < 8; ++k) {
+    const int p = lo + k;
+    if (p <= hi && c[min(p, hi)] == code) found = first + p;
+  }
+  return found;
 }
 
 // ---------------------------------------------------------------- selection core
