@@ -122,6 +122,10 @@ __device__ __forceinline__ const void* uniform_ptr(const void* p) {
   const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
   return (const void*)(uintptr_t)(((uint64_t)hi << 32) | lo);
 }
+__device__ __forceinline__ void dma_to_lds(uint32_t lds, uint32_t off, const void* base) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base)
+               : "memory", "m0");
+}
 template <int NA, int NB>
 __device__ __forceinline__ void load_stage_u(unsigned char* stage, int wave, const bf16_t* A, const int* a_off,
                                              const bf16_t* const* Bp, const int* b_off, int k0, int a_bytes) {
@@ -297,7 +301,122 @@ gemm_bf16_kernel(const bf16_t* __restrict__ A, int lda, const int* __restrict__ 
   // compile time, so the compiler sees that a step's DMA and fragment reads
   // touch different objects and inserts no waits between them.
   // nk is even (each k-range is a multiple of 128, checked on the host)
-  if constexpr (NS > 2) {
+  if constexpr (NS > 2 && TM + TN <= 4) {
+  // Register-ahead pipeline (wave tiles small enough to hold two k-tiles of
+  // fragments): while a k-tile's MFMAs issue from registers, the next one's
+  // fragments are on their way from LDS and the NS - 1 after it from memory, so
+  // a step costs its MFMA chain and one barrier instead of the sum of the
+  // barrier, the LDS latency and the chain.  Stage kt % NS is free once every
+  // wave holds k-tile kt's fragments, which the barrier of step kt tells; the
+  // DMA that refills it issues between the MFMAs.
+  constexpr int NLOADS = NA + NB;                 // DMA instructions per stage per lane
+  static_assert(NLOADS * (NS - 1) < 64, "vmcnt holds 6 bits");
+  constexpr auto vm_lgkm0 = [](int n) constexpr { return (n & 0xF) | (((n >> 4) & 3) << 14) | (0x7 << 4); };
+  const void* base[NLOADS];
+  uint32_t off[NLOADS];                           // byte offset of this lane's next chunk
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_t*)stn[0]);
+#pragma unroll
+  for (int j = 0; j < NLOADS; ++j) {
+    base[j] = uniform_ptr(j < NA ? A : Bp[j < NA ? 0 : j - NA]);
+    off[j] = (uint32_t)(j < NA ? a_off[j < NA ? j : 0] : b_off[j < NA ? 0 : j - NA]) * 2u;
+  }
+  auto load1 = [&](int j, uint32_t stage) {       // DMA instruction j of the next k-tile
+    dma_to_lds(lds0 + stage + (j < NA ? (wave * NA + j) * 1024 : T::A_BYTES + (wave * NB + j - NA) * 1024), off[j],
+               base[j]);
+    off[j] += 128u;
+  };
+  // fragment address: rows 32 apart share their swizzle, so one offset per
+  // k-step serves every block of the wave
+  const int ra = wave_m * TM * 32 + fr, rb = wave_n * TN * 32 + fr;
+  int ao[4], bo[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    ao[kk] = ra * 128 + (((kk * 2 + fc) ^ swz(ra)) << 4);
+    bo[kk] = T::A_BYTES + rb * 128 + (((kk * 2 + fc) ^ swz(rb)) << 4);
+  }
+  bf16x8_t fa[2][4][TM], fb[2][4][TN];
+  auto read = [&](uint32_t stage, auto Set) {
+    constexpr int set = decltype(Set)::value;
+    const unsigned char* st = stn[0] + stage;
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) fa[set][kk][i] = *reinterpret_cast<const bf16x8_t*>(st + ao[kk] + i * 4096);
+#pragma unroll
+      for (int j = 0; j < TN; ++j) fb[set][kk][j] = *reinterpret_cast<const bf16x8_t*>(st + bo[kk] + j * 4096);
+    }
+  };
+  auto mma = [&](int kk, auto Set) {
+    constexpr int set = decltype(Set)::value;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][kk][i], fb[set][kk][j], acc[i][j], 0, 0, 0);
+  };
+  auto barrier = [] {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+    if (s < nk)
+#pragma unroll
+      for (int j = 0; j < NLOADS; ++j) load1(j, s * T::STAGE);
+  asm volatile("" ::: "memory");
+  if (nk >= NS) __builtin_amdgcn_s_waitcnt(vm_lgkm0(NLOADS * (NS - 1)));
+  else __builtin_amdgcn_s_waitcnt(vm_lgkm0(0));
+  barrier();
+  read(0, std::integral_constant<int, 0>{});
+  uint32_t st_cur = 0, st_next = T::STAGE;        // stages of k-tiles kt and kt + 1
+  auto advance = [&]() {
+    st_cur = st_next;
+    st_next = st_next + T::STAGE == (uint32_t)NS * T::STAGE ? 0u : st_next + T::STAGE;
+  };
+  int kt = 0;
+  // steps whose refill lies inside the k range, two at a time (one per register set)
+  for (; kt + 1 + NS < nk; kt += 2) {
+    static_for<2>([&](auto S) {
+      constexpr int cur = decltype(S)::value;
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(vm_lgkm0(NLOADS * (NS - 2)));
+      barrier();
+      read(st_next, std::integral_constant<int, cur ^ 1>{});
+      __builtin_amdgcn_sched_barrier(0);
+      static_for<4>([&](auto KK) {
+        constexpr int kk = decltype(KK)::value;
+        mma(kk, S);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = kk * NLOADS / 4; j < (kk + 1) * NLOADS / 4; ++j) load1(j, st_cur);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      advance();
+    });
+  }
+  for (; kt < nk; kt += 2) {
+    static_for<2>([&](auto S) {
+      constexpr int cur = decltype(S)::value;
+      const int k = kt + cur;
+      if (k + 1 < nk) {
+        asm volatile("" ::: "memory");
+        if (k + NS - 1 < nk) __builtin_amdgcn_s_waitcnt(vm_lgkm0(NLOADS * (NS - 2)));
+        else __builtin_amdgcn_s_waitcnt(vm_lgkm0(0));
+        barrier();
+        read(st_next, std::integral_constant<int, cur ^ 1>{});
+        if (k + NS < nk)
+#pragma unroll
+          for (int j = 0; j < NLOADS; ++j) load1(j, st_cur);
+      }
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) mma(kk, S);
+      advance();
+    });
+  }
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  } else if constexpr (NS > 2) {
   // NS-stage pipeline (small row counts, where each k-tile's weights arrive
   // cold from HBM): stage s of round kt0 computes k-tile kt0+s while the DMA of
   // k-tiles up to kt0+s+NS-1 is in flight; at each stage end the wave waits
