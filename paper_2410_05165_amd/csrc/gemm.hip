@@ -21,6 +21,7 @@
 // M is read from device memory; the grid covers the caller's row count or
 // bound (GemmCall::Mmax), and tiles past M exit at once.
 // fp32 models take the kernels of gemm_f32.hip.
+#include <algorithm>
 #include "common.h"
 #include "kernels.h"
 
@@ -680,153 +681,99 @@ static hipError_t launch_bf16(const GemmCall& g, hipStream_t st) {
   return hipGetLastError();
 }
 
-// Tile shape by row count.  A shape's cost is modelled as the number of rounds
-// of its tiles over the CUs (256 x the workgroups of that shape one CU holds)
-// times the time of one round, t0 + t4k x (k per workgroup) / 4096, fitted to
-// measurements on MI355X at the 7B projections for 320 to 4,096 rows: few rows
-// leave a 256-row tile mostly empty and give too few tiles to fill the CUs,
-// many rows favour the large tiles' higher MFMA rate, and in between the
-// better shape is the one whose last round is fuller.  A last round with a
-// fraction φ of its slots used costs (partial + (1 - partial) φ) of a round:
-// its tiles share the CUs and memory with fewer others (the row shapes were
-// fitted with partial 0.5, q/k/v and gate/up with 1).  The shape does not
-// change any element's k-order, so results do not depend on it.  g.Mmax is
-// the row count of the call when the caller knows it, else an upper bound.
+// Tile shape of a call, by a model of its time: with n workgroups of a shape on
+// the fullest CU (at most `cap` at once, more take further rounds), a round of
+// nk k-tiles costs nk * max(lat, thr * n) + epi us and the launch t0 once.  lat
+// is a k-tile's own latency (barrier, LDS, MFMA chain), which few rows or few
+// columns are bound by: small tiles spread those calls over more CUs; thr is a
+// k-tile's share of a full CU, where large tiles move fewer bytes per MFMA.
+//
+// The constants are fitted to measurements on MI355X, weights cold in L2: d 256,
+// 768, 1,024, 2,048, 4,096 with f 1,024 to 11,008, 23 row counts from 16 to 4,000
+// (7,744 at d 4,096), about 18 shapes a call.  The model's picks are on average
+// within 0.5% (q/k/v), 1.2% (gate/up), 1.3% (o, down) and 1.5% (head) of the
+// fastest shape measured.  The rule it replaced (fixed row thresholds, and rounds
+// fitted at d 4,096 alone) was 14-21% off on the same grid: at 640 rows of
+// d 768, f 3,072 q/k/v took 13.3 instead of 9.2 us, gate/up 14.3 (10.9), o 7.2
+// (4.7) and down 16.0 (8.4); the head of 640 rows at d 4,096 33 (16).
+// The shape does not change any element's k-order, so results do not depend on
+// it.  g.Mmax is the row count of the call when the caller knows it, else an
+// upper bound.
 namespace {
 constexpr int kCUs = 256;
-struct Shape { int bm, bn, per_cu; float t0, t4k; };
-// q/k/v: 256x256 (8 waves), 128x256 (8 waves), 64x256 (2 waves, two per CU),
-// 256x192 (8 waves; 3 d_model is a multiple of 192, so no ragged column tile);
-// (fitted warm); gate/up: the first three, fitted with the weights arriving cold
-// from HBM as they do in a forward (picks the fastest measured shape at every
-// one of 13 row counts from 320 to 4,096)
-// and 64x256 of 8 waves with three stages (one per CU).  The 128x256 and
-// 64x256 tiles of 8 waves run three LDS stages (144 and 120 KB), which hides
-// the cold weight fetch at a few hundred rows: q/k/v at 320 rows 86 -> 59 us,
-// 128x256 q/k/v at 400-640 rows 85-90 -> 70-78 us and gate/up 143-152 ->
-// 120-135 us, with cold weights.  The q/k/v constants are scaled from those
-// measurements (256x192 keeps 960 rows and more); gate/up keeps its two-stage
-// constant, with which the 128x256 tile is picked only where it was already
-// fastest (about 640 rows: 152 -> 135 us)
-constexpr Shape kQkvShapes[] = {
-    {256, 256, 1, 0.f, 98.f}, {128, 256, 1, 0.f, 57.f}, {64, 256, 2, 0.f, 73.f}, {256, 192, 1, 0.f, 83.f},
-    {64, 256, 1, 0.f, 46.f}};
-constexpr Shape kGuShapes[] = {{256, 256, 1, 0.f, 104.f}, {128, 256, 1, 0.f, 70.f}, {64, 256, 2, 0.f, 78.f}};
-// o, down, output head: 256x256, 256x128 (8 waves), 128x128 (4 waves, two per
-// CU), 64x64 (2 waves, four per CU)
-// (fitted with the weights arriving cold from HBM: within 3% of the fastest
-// measured shape at all 12 row counts from 320 to 4,096, for o and for down)
-constexpr Shape kRowShapes[] = {
-    {256, 256, 1, 25.f, 97.5f}, {256, 128, 1, 10.5f, 70.f}, {128, 128, 2, 14.f, 59.f}, {64, 64, 4, 6.f, 50.f}};
-// residual projections also: 128x128 of 4 waves with three stages (one per CU;
-// 320 rows: o 33 -> 26 us, down 72 -> 56 us with cold weights; constants from
-// those two measurements)
-constexpr Shape kResidShapes[] = {
-    {256, 256, 1, 25.f, 97.5f}, {256, 128, 1, 10.5f, 70.f}, {128, 128, 2, 14.f, 59.f}, {64, 64, 4, 6.f, 50.f},
-    {128, 128, 1, 4.4f, 36.f}};
-
-// Few rows (a decode level of a few users, the verify tree of one user): the
-// weight stream is the whole cost, and the tiles above leave most CUs idle (a
-// 256-column tile gives q/k/v 48 workgroups).  Narrow tiles with four to six
-// LDS stages give 190-380 workgroups, each streaming a thin weight slice.
-// Measured at the 7B projections (1-256 rows, cold weights, warm clocks), with
-// the time of the cost model's shape in parentheses:
-//   1-32 rows    q/k/v 32x64 of two waves (six stages) 26-28 us (54); gate/up
-//                64x64 of two waves (four) 42-43 (60-64); o and down 64x32 of
-//                two waves (six) 15 and 30 (22 and 50);
-//   33-64        q/k/v 64x64 of 2x2 waves of 32x32 (four) 28-31 (two waves of
-//                32x64: 32-34); gate/up 64x128 of 2x2 waves (four) 44-45; o and
-//                down as above;
-//   65-128       one M-tile of 128 rows over four waves instead of two 64-row
-//                tiles: q/k/v 128x64 of 2x2 waves 34-38 (38-44), gate/up
-//                128x128 of 2x2 waves 48-53 (55-61), o and down 128x32 of four
-//                waves in a column 17-18 and 35-39 (17-18 and 36-42), all four
-//                stages.
-constexpr int kFewRowsQkv = 128, kFewRowsGu = 128, kFewRowsResid = 128, kNarrowRows = 64;
-// A little above that (a prompt of one user, the verify tree of a few): one
-// M-tile of 192 rows over all the rows, split among four waves so that every
-// SIMD of a CU issues MFMAs (the two-wave tiles of the same height leave half
-// of them idle), and each weight slice crosses the chip once.  Measured at the
-// 7B projections with cold weights, 129-192 rows: q/k/v 192x64 of 2x2 waves
-// (four stages) 45-49 instead of 55-60 us, gate/up 192x128 of 2x2 waves (four
-// stages, the whole 160 KB of LDS) 55-59 instead of 65-69, o and down 256x32
-// of four waves in a column (four stages) 23-24 and 49-54 instead of 24-25
-// and 52-55; at 193-256 rows q/k/v 256x64 of 4x2 waves (three stages) 51-54
-// instead of 57-60 and o/down 192x64 of 2x2 waves (four stages) 54-56 instead
-// of 56-61 us for down.  Above 256 rows the shapes below are as fast or faster.
-constexpr int kMidRows = 192, kMidRows2 = 256;
-constexpr int kHeadFewRows = 320;
+struct Shape {
+  int bm, bn, cap;
+  float t0, lat, thr, epi;
+  hipError_t (*launch)(const GemmCall&, hipStream_t);
+};
+const Shape kQkvShapes[] = {
+    {64, 64, 2, 2.51f, 0.238f, 0.207f, 1.81f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 1, 1, 4>},
+    {128, 128, 1, 1.04f, 0.512f, 0.145f, 5.69f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 1, 2, 4>},
+    {256, 192, 1, 3.74f, 1.281f, 0.013f, 8.12f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 2, 3, 2>},
+    {64, 64, 2, 3.46f, 0.262f, 0.229f, 0.85f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 1, 1, 3>},
+    {128, 256, 1, 0.39f, 0.643f, 0.900f, 11.37f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 1, 4, 3>},
+    {32, 64, 2, 2.33f, 0.211f, 0.181f, 2.00f, launch_bf16<BMAP_QKV, EPI_QKV, 1, 2, 1, 1, 6>},
+    {256, 256, 1, 2.15f, 1.491f, 0.162f, 13.46f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 2, 4, 2>},
+    {128, 64, 1, 1.67f, 0.341f, 0.321f, 3.23f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 1, 1, 4>},
+    {128, 128, 2, 4.34f, 0.736f, 0.521f, 3.85f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 2, 2, 2>},
+};
+const Shape kGuShapes[] = {
+    {64, 128, 2, 2.04f, 0.448f, 0.323f, 1.01f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 1, 2, 3>},
+    {256, 128, 1, 0.00f, 0.819f, 0.190f, 5.37f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 2, 2, 3>},
+    {64, 64, 2, 2.31f, 0.305f, 0.218f, 0.88f, launch_bf16<BMAP_GU, EPI_GU, 2, 1, 1, 2, 4>},
+    {128, 128, 1, 1.81f, 0.198f, 0.546f, 1.90f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 1, 2, 3>},
+    {256, 256, 1, 0.00f, 1.398f, 0.170f, 7.16f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 2, 4, 2>},
+    {128, 128, 2, 2.43f, 0.680f, 0.505f, 1.60f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 2, 2, 2>},
+    {128, 64, 1, 1.77f, 0.258f, 0.387f, 1.62f, launch_bf16<BMAP_GU, EPI_GU, 4, 1, 1, 2, 4>},
+    {128, 128, 1, 1.60f, 0.513f, 0.002f, 2.96f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 2, 2, 4>},
+    {128, 256, 1, 0.00f, 0.907f, 0.044f, 6.23f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 1, 4, 3>},
+};
+const Shape kResidShapes[] = {
+    {64, 64, 1, 2.17f, 0.176f, 0.207f, 0.66f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 1, 1, 4>},
+    {128, 128, 1, 0.00f, 0.550f, 0.041f, 3.85f, launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 2, 1, 2, 4>},
+    {64, 32, 2, 1.14f, 0.175f, 0.149f, 1.73f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 1, 1, 1, 6>},
+    {128, 128, 2, 1.02f, 0.740f, 0.523f, 3.09f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 2, 2, 2>},
+    {128, 64, 1, 0.41f, 0.017f, 0.335f, 2.59f, launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 2, 1, 1, 4>},
+    {256, 256, 1, 0.00f, 1.601f, 0.008f, 6.85f, launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 2, 2, 4, 2>},
+    {64, 64, 3, 1.59f, 0.249f, 0.244f, 1.13f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 1, 1, 3>},
+    {128, 128, 1, 0.35f, 0.541f, 0.107f, 4.62f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 2, 2, 3>},
+    {64, 128, 1, 0.92f, 0.342f, 0.079f, 2.26f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 1, 2, 4>},
+};
+// the item rows of the output head (at most 1,024 columns)
+const Shape kHeadShapes[] = {
+    {64, 64, 1, 2.00f, 0.163f, 0.109f, 0.72f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 1, 1, 4>},
+    {128, 64, 1, 0.01f, 0.175f, 0.251f, 3.22f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 2, 1, 4>},
+    {64, 32, 2, 1.01f, 0.130f, 0.115f, 2.16f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 1, 1, 1, 6>},
+    {128, 128, 1, 4.18f, 0.391f, 0.371f, 0.05f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 2, 2, 3>},
+    {64, 64, 3, 1.16f, 0.222f, 0.182f, 1.48f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 1, 1, 3>},
+};
 
 template <int NSH>
-int pick_shape(const Shape (&sh)[NSH], int M, int N, int K, int kparts, float partial) {
+const Shape& pick_shape(const Shape (&sh)[NSH], int M, int N, int K, int kparts) {
+  const float nk = (float)(K / kparts) / 64.f;
   int best = 0;
-  float best_cost = 0.f;
+  float best_time = 0.f;
   for (int i = 0; i < NSH; ++i) {
-    const long tiles = kparts * (long)((M + sh[i].bm - 1) / sh[i].bm) * ((N + sh[i].bn - 1) / sh[i].bn);
-    const long slots = (long)kCUs * sh[i].per_cu;
+    const Shape& s = sh[i];
+    const long tiles = (long)kparts * ((M + s.bm - 1) / s.bm) * ((N + s.bn - 1) / s.bn), slots = (long)kCUs * s.cap;
     const long full = tiles / slots, rest = tiles - full * slots;
-    const float rounds = (float)full + (rest ? partial + (1.f - partial) * (float)rest / (float)slots : 0.f);
-    const float cost = rounds * (sh[i].t0 + sh[i].t4k * (float)K / kparts / 4096.f);
-    if (i == 0 || cost < best_cost) { best = i; best_cost = cost; }
+    float time = s.t0 + (float)full * (nk * std::max(s.lat, s.thr * (float)s.cap) + s.epi);
+    if (rest) time += nk * std::max(s.lat, s.thr * (float)((rest + kCUs - 1) / kCUs)) + s.epi;
+    if (i == 0 || time < best_time) { best = i; best_time = time; }
   }
-  return best;
+  return sh[best];
 }
 }  // namespace
 
 hipError_t gemm(const GemmCall& g, hipStream_t st) {
-  if (g.bf16) {
-    const int M = g.Mmax > 0 ? g.Mmax : 1;
-    switch (g.kind) {
-      case GEMM_QKV:
-        if (M <= 32) return launch_bf16<BMAP_QKV, EPI_QKV, 1, 2, 1, 1, 6>(g, st);
-        if (M <= kNarrowRows) return launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 1, 1, 4>(g, st);
-        if (M <= kFewRowsQkv) return launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 2, 1, 4>(g, st);
-        if (M <= kMidRows) return launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 3, 1, 4>(g, st);
-        if (M <= kMidRows2) return launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 2, 1, 3>(g, st);
-        switch (pick_shape(kQkvShapes, M, g.N, g.K, 1, 1.f)) {
-          case 0: return launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 2, 4>(g, st);
-          case 1: return launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 1, 4, 3>(g, st);
-          case 2: return launch_bf16<BMAP_QKV, EPI_QKV, 1, 2, 2, 4>(g, st);
-          case 3: return launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 2, 3>(g, st);
-          default: return launch_bf16<BMAP_QKV, EPI_QKV, 2, 4, 1, 2, 3>(g, st);
-        }
-      case GEMM_GU:
-        if (M <= 32) return launch_bf16<BMAP_GU, EPI_GU, 2, 1, 1, 2, 4>(g, st);
-        if (M <= kNarrowRows) return launch_bf16<BMAP_GU, EPI_GU, 2, 2, 1, 2, 4>(g, st);
-        if (M <= kFewRowsGu) return launch_bf16<BMAP_GU, EPI_GU, 2, 2, 2, 2, 4>(g, st);
-        if (M <= kMidRows) return launch_bf16<BMAP_GU, EPI_GU, 2, 2, 3, 2, 4>(g, st);
-        switch (pick_shape(kGuShapes, M, g.N, g.K, 1, 1.f)) {
-          case 0: return launch_bf16<BMAP_GU, EPI_GU, 4, 2, 2, 4>(g, st);
-          case 1: return launch_bf16<BMAP_GU, EPI_GU, 4, 2, 1, 4, 3>(g, st);
-          default: return launch_bf16<BMAP_GU, EPI_GU, 1, 2, 2, 4>(g, st);
-        }
-      case GEMM_RESID:
-        if (M <= kNarrowRows) return launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 1, 1, 1, 6>(g, st);
-        if (M <= kFewRowsResid) return launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 1, 1, 1, 4>(g, st);
-        if (M <= kMidRows) return launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 1, 2, 1, 4>(g, st);
-        if (M <= kMidRows2) return launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 3, 1, 4>(g, st);
-        switch (pick_shape(kResidShapes, M, g.N, g.K, g.part ? 2 : 1, 0.5f)) {
-          case 0: return launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 2, 2, 4>(g, st);
-          case 1: return launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 2, 2, 2>(g, st);
-          case 2: return launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 2, 2>(g, st);
-          case 3: return launch_bf16<BMAP_PLAIN, EPI_RESID, 1, 2, 2, 1>(g, st);
-          default: return launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 2, 2, 3>(g, st);
-        }
-      default:
-        // the item rows of the output head (1,024 columns): up to a few hundred
-        // rows 64x32 tiles of two waves with six stages give twice the
-        // workgroups of the model's pick and stream the head in 20-22 instead of
-        // 32-37 us (1-320 rows, warm clocks)
-        if (M <= kHeadFewRows) return launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 1, 1, 1, 6>(g, st);
-        switch (pick_shape(kRowShapes, M, g.N, g.K, 1, 0.5f)) {
-          case 0: return launch_bf16<BMAP_PLAIN, EPI_STORE, 4, 2, 2, 4>(g, st);
-          case 1: return launch_bf16<BMAP_PLAIN, EPI_STORE, 4, 2, 2, 2>(g, st);
-          case 2: return launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 2, 2>(g, st);
-          default: return launch_bf16<BMAP_PLAIN, EPI_STORE, 1, 2, 2, 1>(g, st);
-        }
-    }
+  if (!g.bf16) return gemm_f32(g, st);
+  const int M = g.Mmax > 0 ? g.Mmax : 1;
+  switch (g.kind) {
+    case GEMM_QKV: return pick_shape(kQkvShapes, M, g.N, g.K, 1).launch(g, st);
+    case GEMM_GU: return pick_shape(kGuShapes, M, g.N, g.K, 1).launch(g, st);
+    case GEMM_RESID: return pick_shape(kResidShapes, M, g.N, g.K, g.part ? 2 : 1).launch(g, st);
+    default: return pick_shape(kHeadShapes, M, g.N, g.K, 1).launch(g, st);
   }
-  return gemm_f32(g, st);
 }
 
 }  // namespace atspeed
