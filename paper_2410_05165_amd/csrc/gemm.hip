@@ -8,8 +8,8 @@
 //   QKV   rotary embedding on q and k, rounding to bf16, q to its row buffer,
 //         k/v scattered into the prefix cache or the tree KV buffer.  The tile's
 //         weight rows are interleaved (qkv_logical) so that a column's
-//         rotate-half partner is lane ^ 16 of the same MFMA block, one
-//         v_permlane16_swap away whatever the tile width;
+//         rotate-half partner is in the same MFMA block, and with the operands
+//         swapped in the same lane, whatever the tile width;
 //   GU    gate and up columns share a tile (first/second half of each wave's
 //         blocks), out = bf16(SiLU(gate) * up);
 //   RESID residual stream x += acc (fp32); with a partial buffer the k range
@@ -39,7 +39,7 @@ struct EpiArgs {
   bf16_t* q;         // [M, d]
   bf16_t* kdst;      // prefix cache or tree KV base of this layer
   bf16_t* vdst;
-  const float* ropeT; // [max_pos][16][4] (cos, sin), rotary index 16*b + i at [pos][i][b]
+  const float* ropeT; // [max_pos][d_head / 2] (cos, sin)
   Rows rows;
   int kv_mode;       // 0 prefix cache [B][H][Pmax][dh], 1 tree [slot][d]
   int Pmax;
@@ -77,8 +77,8 @@ __device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
 
 // Column order of the q/k/v product (bf16 path).  Within each head, the 32
 // columns of MFMA block b hold rotary indices 16b .. 16b+15 of the head's first
-// half in lanes 0..15 and the same indices of its second half in lanes 16..31,
-// so every column's rotate-half partner is lane ^ 16 of the same block.  Maps a
+// half at 0..15 and the same indices of its second half at 16..31, so every
+// column's rotate-half partner is 16 away in the same block.  Maps a
 // column's place pp within its head (as the tile holds it) to its column in
 // the head (d_head 64 or 128); a bijection on 0 .. d_head-1 that keeps runs of
 // 16 columns, and so 16-byte chunks of the bf16 output, contiguous.
@@ -145,10 +145,19 @@ __device__ __forceinline__ void load_stage_u(unsigned char* stage, int wave, con
   }
 }
 
+// acc + A W^T of one 32x32 block.  Swapped, the block's transpose: each lane then
+// holds four consecutive output columns of a row at a time instead of one column
+// of many rows (the same products in the same order, so the same bits).
+template <bool SWAP>
+__device__ __forceinline__ f32x16_t mfma(bf16x8_t a, bf16x8_t w, f32x16_t acc) {
+  return SWAP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, a, acc, 0, 0, 0)
+              : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, w, acc, 0, 0, 0);
+}
+
 // One LDS stage (64 columns of k) through the MFMAs.  Fragments of k-step kk+1
 // are read into a second register set while the MFMAs of step kk issue, so the
 // LDS latency hides behind matrix work instead of stalling every step.
-template <int WM, int WN, int TM, int TN>
+template <int TM, int TN, bool SWAP>
 __device__ __forceinline__ void mma_stage(const unsigned char* stage, int wave_m, int wave_n, int fr, int fc,
                                           f32x16_t (&acc)[TM][TN], int a_bytes) {
   bf16x8_t af[2][TM], bfr[2][TN];
@@ -178,7 +187,7 @@ __device__ __forceinline__ void mma_stage(const unsigned char* stage, int wave_m
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[cur][i], bfr[cur][j], acc[i][j], 0, 0, 0);
+        acc[i][j] = mfma<SWAP>(af[cur][i], bfr[cur][j], acc[i][j]);
     if constexpr (kk + 1 < 4) {
       static_for<TM + TN>([&](auto) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
@@ -197,14 +206,18 @@ gemm_bf16_kernel(const bf16_t* __restrict__ A, int lda, const int* __restrict__ 
                  BArgs b, EpiArgs e) {
   using T = Tile<WM, WN, TM, TN>;
   constexpr int NW = WM * WN;
+  constexpr bool SWAP = EPI == EPI_GU || EPI == EPI_QKV;   // the outputs that are written in bf16
   static_assert(NW == 1 || NW == 2 || NW == 4 || NW == 8, "one, two, four or eight waves");
   static_assert(NS >= 2 && NS <= 8, "two to eight LDS stages");
   constexpr int NA = T::BM / (8 * NW);   // wave instructions per stage for A (8 rows of 128 B each)
   constexpr int NB = T::BN / (8 * NW);
+  constexpr bool WIDE = NS == 2 && NW == 4 && TM + TN >= 6;   // one wave per SIMD
   // two stages: two named arrays (see the pipeline below); more: one array of NS
-  __shared__ __align__(1024) unsigned char st0[NS == 2 ? T::STAGE : 16];
-  __shared__ __align__(1024) unsigned char st1[NS == 2 ? T::STAGE : 16];
-  __shared__ __align__(1024) unsigned char stn[NS > 2 ? NS : 1][NS > 2 ? T::STAGE : 16];
+  constexpr bool ONE = NS > 2 || WIDE;
+  __shared__ size_t kvrow[EPI == EPI_QKV ? T::BM : 1];   // K/V destination of each tile row (its head 0)
+  __shared__ __align__(1024) unsigned char st0[ONE ? 16 : T::STAGE];
+  __shared__ __align__(1024) unsigned char st1[ONE ? 16 : T::STAGE];
+  __shared__ __align__(1024) unsigned char stn[ONE ? NS : 1][ONE ? T::STAGE : 16];
   const int M = *Mdev;
   // XCD-aware tile order: workgroup L is dispatched to XCD L % 8; XCD x owns the
   // contiguous range x*per .. x*per+per-1 of the tiles.  Tiles are numbered in
@@ -302,7 +315,126 @@ gemm_bf16_kernel(const bf16_t* __restrict__ A, int lda, const int* __restrict__ 
   // compile time, so the compiler sees that a step's DMA and fragment reads
   // touch different objects and inserts no waits between them.
   // nk is even (each k-range is a multiple of 128, checked on the host)
-  if constexpr (NS > 2 && TM + TN <= 4) {
+  if constexpr (WIDE) {
+  // The largest tiles: four waves of up to 128x128, one per SIMD with its 512
+  // registers, which reads the fewest LDS bytes per MFMA.  Nothing else hides a
+  // wave's waits, so every instruction has a place between two MFMAs:
+  //  - a k-step's fragments are read during the step before it, also across
+  //    k-tiles: the barrier stands before a k-tile's last step, once every wave has
+  //    read its fragments and written its share of the next k-tile;
+  //  - k-tiles come through registers, a 16-byte chunk at a time, its LDS write
+  //    and the load that refills its register spread evenly over the MFMAs, so a
+  //    load has a whole k-tile's time to arrive.  Six loads in a row keep the
+  //    vector memory path busy longer than the MFMAs between them (2,610 instead
+  //    of 2,320 cycles a k-tile at 256x256, 2,048 of them MFMA); direct
+  //    global->LDS DMA, which must wait for the stage to be free, took 3,000-4,000
+  //    where the lines miss L2.
+  constexpr int NLOADS = NA + NB, SLOTS = TM * TN;
+  // chunk w goes after MFMA slot_of(w) of the 4 SLOTS from a barrier to the next
+  constexpr auto slot_of = [](int w) constexpr { return w * 4 * SLOTS / NLOADS + 2; };
+  constexpr int EARLY = [=]() constexpr { int n = 0; while (n < NLOADS && slot_of(n) < SLOTS) ++n; return n; }();
+  uint32_t off[NLOADS];
+#pragma unroll
+  for (int j = 0; j < NLOADS; ++j)
+    off[j] = (uint32_t)(j < NA ? a_off[j < NA ? j : 0] : b_off[j < NA ? 0 : j - NA]) * 2u;
+  u32x4_t stg[NLOADS];
+  const __amdgpu_buffer_rsrc_t ars = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(A), 0, -1, 0x00020000);
+  __amdgpu_buffer_rsrc_t brs[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+    brs[j] = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(uniform_ptr(Bp[j])), 0, -1, 0x00020000);
+  auto gload = [&](int j, int kt) {
+    stg[j] = __builtin_amdgcn_raw_buffer_load_b128(j < NA ? ars : brs[j < NA ? 0 : j - NA], (int)off[j], kt * 128, 0);
+  };
+  auto swrite = [&](int j, int buf) {
+    unsigned char* const d = j < NA ? stn[buf] + wave * NA * 1024 + lane * 16 + j * 1024
+                                    : stn[buf] + T::A_BYTES + wave * NB * 1024 + lane * 16 + (j - NA) * 1024;
+    *reinterpret_cast<u32x4_t*>(d) = stg[j];
+  };
+  const int ra = wave_m * TM * 32 + fr, rb = wave_n * TN * 32 + fr;
+  const unsigned char* ap[2][4];
+  const unsigned char* bp[2][4];
+#pragma unroll
+  for (int b2 = 0; b2 < 2; ++b2)
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+      ap[b2][kk] = stn[b2] + ra * 128 + (((kk * 2 + fc) ^ swz(ra)) << 4);
+      bp[b2][kk] = stn[b2] + T::A_BYTES + rb * 128 + (((kk * 2 + fc) ^ swz(rb)) << 4);
+    }
+  bf16x8_t fa[2][TM], fb[2][TN];
+  // fragment q of a k-step, in the order its MFMAs need them
+  auto read1 = [&](int q, int buf, int kk, int set) {
+    if (q == 0) fa[set][0] = *reinterpret_cast<const bf16x8_t*>(ap[buf][kk]);
+    else if (q <= TN) fb[set][q - 1] = *reinterpret_cast<const bf16x8_t*>(bp[buf][kk] + (q - 1) * 4096);
+    else fa[set][q - TN] = *reinterpret_cast<const bf16x8_t*>(ap[buf][kk] + (q - TN) * 4096);
+  };
+  auto barrier = [] {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+#pragma unroll
+  for (int j = 0; j < NLOADS; ++j) gload(j, 0);
+#pragma unroll
+  for (int j = 0; j < NLOADS; ++j) {
+    swrite(j, 0);
+    gload(j, 1);
+  }
+#pragma unroll
+  for (int j = 0; j < EARLY; ++j) {
+    swrite(j, 1);
+    if (nk > 2) gload(j, 2);
+  }
+  barrier();
+  static_for<TM + TN>([&](auto Q) { read1(decltype(Q)::value, 0, 0, 0); });
+  // k-tile kt; Left: k-tiles after it, at most 3 (more make no difference)
+  auto ktile = [&](auto Buf, auto Left, int kt) {
+    constexpr int buf = decltype(Buf)::value, left = decltype(Left)::value;
+    static_for<4>([&](auto KK) {
+      constexpr int kk = decltype(KK)::value, cur = kk & 1, nxt = cur ^ 1;
+      if constexpr (kk == 3 && left > 0) barrier();
+      static_for<SLOTS>([&](auto Q) {
+        constexpr int q = decltype(Q)::value, i = q / TN, j = q % TN;
+        acc[i][j] = mfma<SWAP>(fa[cur][i], fb[cur][j], acc[i][j]);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (q < TM + TN) {
+          if constexpr (kk < 3) read1(q, buf, kk + 1, nxt);
+          else if constexpr (left > 0) read1(q, buf ^ 1, 0, nxt);
+        }
+        // after the barrier k-tile kt + 2's first chunks go to the stage this
+        // k-tile has left, before it k-tile kt + 1's others to the other one
+        constexpr int slot = ((kk + 1) & 3) * SLOTS + q;
+        static_for<NLOADS>([&](auto W) {
+          constexpr int w = decltype(W)::value;
+          if constexpr (slot_of(w) == slot) {
+            if constexpr (left > (kk < 3 ? 0 : 1)) {
+              swrite(w, kk < 3 ? buf ^ 1 : buf);
+              __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (left > (kk < 3 ? 1 : 2)) gload(w, kt + (kk < 3 ? 2 : 3));
+          }
+        });
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    });
+  };
+  typedef std::integral_constant<int, 0> I0;
+  typedef std::integral_constant<int, 1> I1;
+  typedef std::integral_constant<int, 2> I2;
+  typedef std::integral_constant<int, 3> I3;
+  int kt = 0;
+  for (; kt + 4 < nk; kt += 2) {
+    ktile(I0{}, I3{}, kt);
+    ktile(I1{}, I3{}, kt + 1);
+  }
+  if (kt + 4 == nk) {
+    ktile(I0{}, I3{}, kt);
+    ktile(I1{}, I2{}, kt + 1);
+  }
+  ktile(I0{}, I1{}, nk - 2);
+  ktile(I1{}, I0{}, nk - 1);
+  __syncthreads();
+  } else if constexpr (NS > 2 && TM + TN <= 4) {
   // Register-ahead pipeline (wave tiles small enough to hold two k-tiles of
   // fragments): while a k-tile's MFMAs issue from registers, the next one's
   // fragments are on their way from LDS and the NS - 1 after it from memory, so
@@ -353,7 +485,7 @@ gemm_bf16_kernel(const bf16_t* __restrict__ A, int lda, const int* __restrict__ 
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[set][kk][i], fb[set][kk][j], acc[i][j], 0, 0, 0);
+        acc[i][j] = mfma<SWAP>(fa[set][kk][i], fb[set][kk][j], acc[i][j]);
   };
   auto barrier = [] {
     asm volatile("" ::: "memory");
@@ -449,7 +581,7 @@ gemm_bf16_kernel(const bf16_t* __restrict__ A, int lda, const int* __restrict__ 
           load_stage_u<NA, NB>(stage(std::integral_constant<int, s_ + NS - 1>{}), wave, A, a_off, Bp, b_off,
                                (kt + NS - 1) * 64, T::A_BYTES);
         __builtin_amdgcn_sched_barrier(0);
-        mma_stage<WM, WN, TM, TN>(stage(S), wave_m, wave_n, fr, fc, acc, T::A_BYTES);
+        mma_stage<TM, TN, SWAP>(stage(S), wave_m, wave_n, fr, fc, acc, T::A_BYTES);
         asm volatile("" ::: "memory");
         if (kt + NS - 1 < nk) __builtin_amdgcn_s_waitcnt(WAITCNT);
         else __builtin_amdgcn_s_waitcnt(WAITALL);
@@ -470,12 +602,12 @@ gemm_bf16_kernel(const bf16_t* __restrict__ A, int lda, const int* __restrict__ 
   for (int kt = 0; kt < nk; kt += 2) {
     load_stage<NA, NB>(st1, wave, A, a_off, Bp, b_off, (kt + 1) * 64, T::A_BYTES);
     __builtin_amdgcn_sched_barrier(0);
-    mma_stage<WM, WN, TM, TN>(st0, wave_m, wave_n, fr, fc, acc, T::A_BYTES);
+    mma_stage<TM, TN, SWAP>(st0, wave_m, wave_n, fr, fc, acc, T::A_BYTES);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
     if (kt + 2 < nk) load_stage<NA, NB>(st0, wave, A, a_off, Bp, b_off, (kt + 2) * 64, T::A_BYTES);
     __builtin_amdgcn_sched_barrier(0);
-    mma_stage<WM, WN, TM, TN>(st1, wave_m, wave_n, fr, fc, acc, T::A_BYTES);
+    mma_stage<TM, TN, SWAP>(st1, wave_m, wave_n, fr, fc, acc, T::A_BYTES);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
   }
@@ -536,119 +668,128 @@ gemm_bf16_kernel(const bf16_t* __restrict__ A, int lda, const int* __restrict__ 
     });
   } else {
     // Results are rounded to bf16 into an LDS copy of the output tile (the stage
-    // buffers are free now), then written out in 16-byte chunks along rows.
+    // buffers are free now), then written out in 16-byte chunks along rows.  With
+    // swapped operands acc[i][j][4 g + r] is row lane % 32, column 8 g + 4 (lane /
+    // 32) + r of block (i, j), so four values make one 8-byte LDS write.  Chunk c of
+    // row r sits at c ^ osw(r), which spreads the 32 rows of a write over the banks.
     constexpr int OUTC = EPI == EPI_GU ? T::BN / 2 : T::BN;  // output columns of the tile
     constexpr int OROW = OUTC * 2;                            // bytes per LDS row
-    // The whole output tile in the first stage buffer when it fits; otherwise
-    // its first half of rows there and the second in the next one.
-    constexpr bool ONEBUF = T::BM * OROW <= T::STAGE;
+    constexpr int CPRW = OUTC / 8;                            // 16-byte chunks per output row
+    constexpr int RSH = OROW >= 256 ? 0 : (OROW == 128 ? 1 : 2);   // rows per 256 bytes, log2
+    constexpr int CMASK = (CPRW % 16 == 0 ? 16 : CPRW % 8 == 0 ? 8 : 4) - 1;
+    static_assert(CPRW % 4 == 0, "whole groups of swizzled chunks");
+    auto osw = [](int r) { return (r >> RSH) & CMASK; };
+    // The whole output tile in the first stage buffer (one array, in the multi-stage
+    // kernels) when it fits; otherwise its first half of rows there and the second
+    // in the next one.
+    constexpr bool ONEBUF = T::BM * OROW <= (ONE ? NS : 1) * T::STAGE;
     constexpr int HROWS = ONEBUF ? T::BM : T::BM / 2;
     constexpr int WMH = ONEBUF ? WM : WM / 2;       // wave rows per buffer
     static_assert(ONEBUF || (HROWS * OROW <= T::STAGE && WM % 2 == 0), "each half of the output tile fits a stage");
-    unsigned char* const ob0 = NS == 2 ? st0 : stn[0];
-    unsigned char* const ob1 = NS == 2 ? st1 : stn[NS > 2 ? 1 : 0];
-    bf16_t* ob = reinterpret_cast<bf16_t*>(wave_m < WMH ? ob0 : ob1);
-    const int hrow0 = (wave_m % WMH) * TM * 32;
+    unsigned char* const ob0 = ONE ? stn[0] : st0;
+    unsigned char* const ob1 = ONE ? stn[0] : st1;
+    unsigned char* const ob = wave_m < WMH ? ob0 : ob1;
+    auto put = [&](int lr, int col, float v0, float v1, float v2, float v3) {   // 4 values at (row of this buffer, column)
+      uint2 w;
+      w.x = (uint32_t)f2bf(v0) | ((uint32_t)f2bf(v1) << 16);
+      w.y = (uint32_t)f2bf(v2) | ((uint32_t)f2bf(v3) << 16);
+      *reinterpret_cast<uint2*>(ob + lr * OROW + (((col >> 3) ^ osw(lr)) << 4) + (col & 4) * 2) = w;
+    };
+    const int hrow0 = (wave_m % WMH) * TM * 32 + fr;          // this lane's row of block 0 in its buffer
     if constexpr (EPI == EPI_GU) {
       constexpr int half = TN / 2;
       static_for<TM>([&](auto I) {
         constexpr int i = decltype(I)::value;
-        static_for<16>([&](auto R) {
-          constexpr int r = decltype(R)::value;
-          const int hr = hrow0 + i * 32 + (r >> 2) * 8 + fc * 4 + (r & 3);  // row within this half
-#pragma unroll
-          for (int j = 0; j < half; ++j) {
-            const int lc = wave_n * (half * 32) + j * 32 + fr;
-            ob[hr * OUTC + lc] = f2bf(silu(acc[i][j][r]) * acc[i][j + half][r]);
-          }
+        static_for<half * 4>([&](auto G) {
+          constexpr int j = decltype(G)::value / 4, g = decltype(G)::value % 4;
+          float v[4];
+          static_for<4>([&](auto R) {
+            constexpr int r = decltype(R)::value;
+            v[r] = silu(acc[i][j][4 * g + r]) * acc[i][j + half][4 * g + r];
+          });
+          put(hrow0 + i * 32, wave_n * (half * 32) + j * 32 + 8 * g + 4 * fc, v[0], v[1], v[2], v[3]);
         });
       });
     } else {  // EPI_QKV: rotary embedding on q and k (column order of qkv_logical)
       // per block (wave-uniform; d_model and d_head are multiples of 32): which of
-      // q, k, v it lies in, and b, its rotary indices being 16b + lane % 16
-      int bsel[TN];
-      bool rotj[TN];
+      // q, k, v it lies in, and its first rotary index; columns 0..15 of a block
+      // and their partners 16..31 are groups g and g + 2 of the same lane
+      for (int r = tid; r < T::BM; r += T::NT) {
+        const int row = m0 + r < M ? m0 + r : M - 1;
+        kvrow[r] = e.kv_mode == 0 ? (size_t)e.rows.user[row] * e.d * e.Pmax + (size_t)e.rows.pos[row] * e.dh
+                                  : (size_t)e.rows.slot[row] * e.d;
+      }
+      int pos[TM];
 #pragma unroll
-      for (int j = 0; j < TN; ++j) {
+      for (int i = 0; i < TM; ++i) {
+        const int row = m0 + (wave_m * TM + i) * 32 + fr;
+        pos[i] = e.rows.pos[row < M ? row : M - 1];
+      }
+      const int halfdh = e.dh >> 1;
+      static_for<TN>([&](auto J) {
+        constexpr int j = decltype(J)::value;
         int pc = col0 + j * 32;
         pc = pc < N ? pc : N - 32;
-        const int wj = pc / e.d;
-        rotj[j] = wj < 2;
-        bsel[j] = ((pc - wj * e.d) & (e.dh - 1)) >> 5;
-      }
-      const bool lo = fr < 16;            // first half of the head: x1 cos - x2 sin, else x2 cos + x1 sin
-      const int i16 = fr & 15;
-      static_for<TM>([&](auto I) {
-        constexpr int i = decltype(I)::value;
-        // rows in groups of 4: positions, then the (cos, sin) pairs of the group's
-        // rows and blocks, all issued before any is used; v columns take cos 1,
-        // sin 0 without a branch
-        static_for<4>([&](auto Q) {
-          constexpr int qg = decltype(Q)::value;
-          int pos[4];
-          static_for<4>([&](auto R) {
-            constexpr int r = decltype(R)::value;
-            const int hr = hrow0 + i * 32 + qg * 8 + fc * 4 + r;
-            const int row = m0 + (wave_m < WMH ? 0 : HROWS) + hr;
-            pos[r] = e.rows.pos[row < M ? row : M - 1];
-          });
-          // (cos, sin) of each row and block: the block's rotary index picks the
-          // pair within the row's table entry by address, so no select on values
-          f32x2_t cs[4][TN];
-          static_for<4>([&](auto R) {
-            constexpr int r = decltype(R)::value;
-            const float* t = e.ropeT + ((size_t)pos[r] * 16 + i16) * 8;
+        const bool rot = pc < 2 * e.d;
+        const int idx0 = ((pc & (e.dh - 1)) >> 1) + 4 * fc;      // d_model is a multiple of d_head
+        static_for<TM>([&](auto I) {
+          constexpr int i = decltype(I)::value;
+          const int lr = hrow0 + i * 32, lc = wave_n * TN * 32 + j * 32 + 4 * fc;
+          if (rot) {
+            // (cos, sin) of the lane's 2 x 4 consecutive rotary indices
+            const float* t = e.ropeT + ((size_t)pos[i] * halfdh + idx0) * 2;
+            f32x4_t cs[4];
 #pragma unroll
-            for (int j = 0; j < TN; ++j) cs[r][j] = *reinterpret_cast<const f32x2_t*>(t + bsel[j] * 2);
-          });
-          static_for<4>([&](auto R) {
-            constexpr int r = decltype(R)::value;
-            constexpr int ra = qg * 4 + r;     // accumulator register of this row
-            const int hr = hrow0 + i * 32 + qg * 8 + fc * 4 + r;
-            static_for<TN>([&](auto J) {
-              constexpr int j = decltype(J)::value;
-              const float v = acc[i][j][ra];
-              // partner = lane ^ 16: v_permlane16_swap of two copies exchanges
-              // the odd 16-lane rows of the first with the even rows of the
-              // second, so the first holds the partner in lanes 16..31 and the
-              // second in lanes 0..15 (a VALU op, no LDS round trip)
-              const auto sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-              const float pv = __uint_as_float(lo ? sw[1] : sw[0]);
-              const float cb = cs[r][j][0], sb = cs[r][j][1];
-              const float c = rotj[j] ? cb : 1.f, sn = rotj[j] ? sb : 0.f;
-              // explicit fma of a rounded product: the same arithmetic in every
-              // tile shape (free contraction may differ between instantiations,
-              // and rows must not depend on the shape their batch got)
-              const float ps = pv * sn;
-              ob[hr * OUTC + wave_n * TN * 32 + j * 32 + fr] = f2bf(__builtin_fmaf(v, c, lo ? -ps : ps));
+            for (int h = 0; h < 4; ++h)
+              cs[h] = *reinterpret_cast<const f32x4_t*>(t + (h >> 1) * 16 + (h & 1) * 4);
+            static_for<2>([&](auto G) {
+              constexpr int g = decltype(G)::value;
+              float y1[4], y2[4];
+              static_for<4>([&](auto R) {
+                constexpr int r = decltype(R)::value;
+                const float x1 = acc[i][j][4 * g + r], x2 = acc[i][j][4 * (g + 2) + r];
+                const float c = cs[2 * g + r / 2][(r & 1) * 2], sn = cs[2 * g + r / 2][(r & 1) * 2 + 1];
+                // explicit fma of a rounded product: the same arithmetic in every
+                // tile shape (free contraction may differ between instantiations,
+                // and rows must not depend on the shape their batch got)
+                const float p1 = x2 * sn, p2 = x1 * sn;
+                y1[r] = __builtin_fmaf(x1, c, -p1);
+                y2[r] = __builtin_fmaf(x2, c, p2);
+              });
+              put(lr, lc + 8 * g, y1[0], y1[1], y1[2], y1[3]);
+              put(lr, lc + 8 * (g + 2), y2[0], y2[1], y2[2], y2[3]);
             });
-          });
+          } else {
+            static_for<4>([&](auto G) {
+              constexpr int g = decltype(G)::value;
+              put(lr, lc + 8 * g, acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+            });
+          }
         });
       });
     }
     __syncthreads();
-    constexpr int CPRW = OUTC / 8;  // 16-byte chunks per output row
+#pragma unroll 2
     for (int c = tid; c < T::BM * CPRW; c += T::NT) {
-      const int lr = c / CPRW, cc = (c % CPRW) * 8;
+      const int lr = c / CPRW, cc = c % CPRW;
       const int row = m0 + lr;
       if (row >= M) continue;
-      const unsigned char* src = (lr < HROWS ? ob0 : ob1) + (lr % HROWS) * OROW + cc * 2;
+      const int br = lr < HROWS ? lr : lr - HROWS;    // row in its buffer
+      const unsigned char* src = (lr < HROWS ? ob0 : ob1) + br * OROW + ((cc ^ osw(br)) << 4);
       const u32x4_t v = *reinterpret_cast<const u32x4_t*>(src);
       if constexpr (EPI == EPI_GU) {
-        const int fcol = tile_n * (T::BN / 2) + cc;
+        const int fcol = tile_n * (T::BN / 2) + cc * 8;
         if (fcol < b.split) *reinterpret_cast<u32x4_t*>(e.hout + (size_t)row * b.split + fcol) = v;
       } else {
-        const int col = tile_n * T::BN + cc;   // 8 columns of the tile's order, one run of qkv_logical
+        const int col = tile_n * T::BN + cc * 8;   // 8 columns of the tile's order, one run of qkv_logical
         if (col >= N) continue;
-        const int which = col / e.d, pc = col - which * e.d, pp = pc & (e.dh - 1);
-        const int hc = pc - pp + qkv_logical(pp, e.dh >> 1);
+        const int which = (col >= e.d) + (col >= 2 * e.d), pc = col - which * e.d, pp = pc & (e.dh - 1);
+        const int hbase = pc - pp, in = qkv_logical(pp, e.dh >> 1);   // first column of the head, column in it
         if (which == 0) {
-          *reinterpret_cast<u32x4_t*>(e.q + (size_t)row * e.d + hc) = v;
+          *reinterpret_cast<u32x4_t*>(e.q + (size_t)row * e.d + hbase + in) = v;
         } else {
-          const int head = hc / e.dh, ii = hc - head * e.dh;
-          size_t off;
-          if (e.kv_mode == 0) off = (((size_t)e.rows.user[row] * e.H + head) * e.Pmax + e.rows.pos[row]) * e.dh + ii;
-          else off = (size_t)e.rows.slot[row] * e.d + hc;
+          // prefix cache: heads Pmax x d_head apart; tree K/V: a row's heads side by side
+          const size_t off = kvrow[lr] + (size_t)hbase * (e.kv_mode == 0 ? e.Pmax : 1) + in;
           *reinterpret_cast<u32x4_t*>((which == 1 ? e.kdst : e.vdst) + off) = v;
         }
       }
@@ -681,6 +822,7 @@ static hipError_t launch_bf16(const GemmCall& g, hipStream_t st) {
   return hipGetLastError();
 }
 
+#ifndef NO_DISPATCH
 // Tile shape of a call, by a model of its time: with n workgroups of a shape on
 // the fullest CU (at most `cap` at once, more take further rounds), a round of
 // nk k-tiles costs nk * max(lat, thr * n) + epi us and the launch t0 once.  lat
@@ -689,10 +831,10 @@ static hipError_t launch_bf16(const GemmCall& g, hipStream_t st) {
 // k-tile's share of a full CU, where large tiles move fewer bytes per MFMA.
 //
 // The constants are fitted to measurements on MI355X, weights cold in L2: d 256,
-// 768, 1,024, 2,048, 4,096 with f 1,024 to 11,008, 23 row counts from 16 to 4,000
-// (7,744 at d 4,096), about 18 shapes a call.  The model's picks are on average
-// within 0.5% (q/k/v), 1.2% (gate/up), 1.3% (o, down) and 1.5% (head) of the
-// fastest shape measured.  The rule it replaced (fixed row thresholds, and rounds
+// 768, 1,024, 2,048, 4,096 with f 1,024 to 11,008, 25 row counts from 10 to 4,800
+// (7,744 at d 4,096), about 17 shapes a call.  The model's picks are on average
+// within 0.2% (q/k/v), 0.4% (gate/up), 2.1% (o, down) and 1.3% (head) of the
+// fastest shape measured.  The rule before it (fixed row thresholds, and rounds
 // fitted at d 4,096 alone) was 14-21% off on the same grid: at 640 rows of
 // d 768, f 3,072 q/k/v took 13.3 instead of 9.2 us, gate/up 14.3 (10.9), o 7.2
 // (4.7) and down 16.0 (8.4); the head of 640 rows at d 4,096 33 (16).
@@ -707,45 +849,54 @@ struct Shape {
   hipError_t (*launch)(const GemmCall&, hipStream_t);
 };
 const Shape kQkvShapes[] = {
-    {64, 64, 2, 2.51f, 0.238f, 0.207f, 1.81f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 1, 1, 4>},
-    {128, 128, 1, 1.04f, 0.512f, 0.145f, 5.69f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 1, 2, 4>},
-    {256, 192, 1, 3.74f, 1.281f, 0.013f, 8.12f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 2, 3, 2>},
-    {64, 64, 2, 3.46f, 0.262f, 0.229f, 0.85f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 1, 1, 3>},
-    {128, 256, 1, 0.39f, 0.643f, 0.900f, 11.37f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 1, 4, 3>},
-    {32, 64, 2, 2.33f, 0.211f, 0.181f, 2.00f, launch_bf16<BMAP_QKV, EPI_QKV, 1, 2, 1, 1, 6>},
-    {256, 256, 1, 2.15f, 1.491f, 0.162f, 13.46f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 2, 4, 2>},
-    {128, 64, 1, 1.67f, 0.341f, 0.321f, 3.23f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 1, 1, 4>},
-    {128, 128, 2, 4.34f, 0.736f, 0.521f, 3.85f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 2, 2, 2>},
+    {32, 64, 2, 2.72f, 0.214f, 0.169f, 1.36f, launch_bf16<BMAP_QKV, EPI_QKV, 1, 2, 1, 1, 6>},
+    {64, 64, 2, 2.43f, 0.245f, 0.172f, 1.40f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 1, 1, 4>},
+    {64, 64, 3, 3.22f, 0.280f, 0.213f, 0.44f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 1, 1, 3>},
+    {128, 64, 1, 1.51f, 0.329f, 0.021f, 2.42f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 1, 1, 4>},
+    {64, 256, 1, 2.29f, 0.612f, 0.076f, 3.12f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 4, 1, 2, 3>},
+    {128, 128, 1, 1.18f, 0.502f, 0.502f, 4.50f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 1, 2, 4>},
+    {128, 128, 2, 3.59f, 0.731f, 0.479f, 2.33f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 2, 2, 2>},
+    {128, 256, 1, 2.27f, 0.794f, 0.536f, 6.46f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 2, 4, 2>},
+    {256, 128, 1, 0.00f, 0.777f, 0.515f, 9.70f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 4, 2, 2>},
+    {192, 192, 1, 0.55f, 0.847f, 0.616f, 9.79f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 3, 3, 2>},
+    {192, 256, 1, 0.00f, 0.998f, 0.309f, 11.65f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 3, 4, 2>},
+    {256, 256, 1, 1.12f, 1.379f, 0.562f, 9.45f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 2, 4, 2>},
 };
 const Shape kGuShapes[] = {
-    {64, 128, 2, 2.04f, 0.448f, 0.323f, 1.01f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 1, 2, 3>},
-    {256, 128, 1, 0.00f, 0.819f, 0.190f, 5.37f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 2, 2, 3>},
-    {64, 64, 2, 2.31f, 0.305f, 0.218f, 0.88f, launch_bf16<BMAP_GU, EPI_GU, 2, 1, 1, 2, 4>},
-    {128, 128, 1, 1.81f, 0.198f, 0.546f, 1.90f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 1, 2, 3>},
-    {256, 256, 1, 0.00f, 1.398f, 0.170f, 7.16f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 2, 4, 2>},
-    {128, 128, 2, 2.43f, 0.680f, 0.505f, 1.60f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 2, 2, 2>},
-    {128, 64, 1, 1.77f, 0.258f, 0.387f, 1.62f, launch_bf16<BMAP_GU, EPI_GU, 4, 1, 1, 2, 4>},
-    {128, 128, 1, 1.60f, 0.513f, 0.002f, 2.96f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 2, 2, 4>},
-    {128, 256, 1, 0.00f, 0.907f, 0.044f, 6.23f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 1, 4, 3>},
+    {64, 64, 2, 2.22f, 0.305f, 0.224f, 0.91f, launch_bf16<BMAP_GU, EPI_GU, 2, 1, 1, 2, 4>},
+    {64, 128, 2, 1.69f, 0.454f, 0.316f, 1.27f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 1, 2, 3>},
+    {128, 64, 1, 1.61f, 0.340f, 0.226f, 1.90f, launch_bf16<BMAP_GU, EPI_GU, 4, 1, 1, 2, 4>},
+    {128, 128, 1, 1.41f, 0.132f, 0.518f, 3.02f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 2, 2, 4>},
+    {128, 128, 1, 1.54f, 0.546f, 0.548f, 2.18f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 1, 2, 3>},
+    {128, 128, 2, 2.34f, 0.719f, 0.507f, 1.92f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 2, 2, 2>},
+    {192, 128, 1, 0.00f, 0.705f, 0.215f, 5.35f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 3, 2, 4>},
+    {128, 256, 1, 0.00f, 0.903f, 0.770f, 6.11f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 1, 4, 3>},
+    {256, 128, 1, 0.00f, 0.803f, 0.830f, 4.96f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 2, 2, 3>},
+    {192, 256, 1, 0.00f, 1.048f, 0.620f, 7.95f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 3, 4, 2>},
+    {256, 256, 1, 0.00f, 1.319f, 0.513f, 10.58f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 4, 4, 2>},
+    {256, 256, 1, 0.00f, 1.464f, 0.505f, 7.44f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 2, 4, 2>},
 };
 const Shape kResidShapes[] = {
-    {64, 64, 1, 2.17f, 0.176f, 0.207f, 0.66f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 1, 1, 4>},
-    {128, 128, 1, 0.00f, 0.550f, 0.041f, 3.85f, launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 2, 1, 2, 4>},
-    {64, 32, 2, 1.14f, 0.175f, 0.149f, 1.73f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 1, 1, 1, 6>},
-    {128, 128, 2, 1.02f, 0.740f, 0.523f, 3.09f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 2, 2, 2>},
-    {128, 64, 1, 0.41f, 0.017f, 0.335f, 2.59f, launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 2, 1, 1, 4>},
-    {256, 256, 1, 0.00f, 1.601f, 0.008f, 6.85f, launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 2, 2, 4, 2>},
-    {64, 64, 3, 1.59f, 0.249f, 0.244f, 1.13f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 1, 1, 3>},
-    {128, 128, 1, 0.35f, 0.541f, 0.107f, 4.62f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 2, 2, 3>},
-    {64, 128, 1, 0.92f, 0.342f, 0.079f, 2.26f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 1, 2, 4>},
+    {64, 32, 2, 0.99f, 0.176f, 0.153f, 1.70f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 1, 1, 1, 6>},
+    {64, 64, 1, 1.84f, 0.172f, 0.227f, 0.61f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 1, 1, 4>},
+    {64, 64, 2, 1.87f, 0.250f, 0.212f, 0.83f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 1, 1, 3>},
+    {64, 128, 1, 0.64f, 0.361f, 0.032f, 2.52f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 1, 2, 4>},
+    {128, 64, 1, 0.18f, 0.336f, 0.042f, 2.63f, launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 2, 1, 1, 4>},
+    {128, 128, 1, 0.00f, 0.204f, 0.513f, 3.95f, launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 2, 1, 2, 4>},
+    {128, 128, 1, 0.00f, 0.494f, 0.268f, 4.29f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 2, 2, 3>},
+    {128, 128, 2, 1.05f, 0.716f, 0.540f, 3.21f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 2, 2, 2>},
+    {128, 256, 1, 0.00f, 0.853f, 0.065f, 6.38f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 2, 4, 2>},
+    {256, 128, 1, 0.00f, 0.826f, 0.749f, 7.28f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 4, 2, 2>},
+    {192, 256, 1, 0.00f, 1.052f, 0.123f, 9.08f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 3, 4, 2>},
+    {256, 256, 1, 0.00f, 1.385f, 0.348f, 10.60f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 4, 4, 2>},
 };
 // the item rows of the output head (at most 1,024 columns)
 const Shape kHeadShapes[] = {
-    {64, 64, 1, 2.00f, 0.163f, 0.109f, 0.72f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 1, 1, 4>},
-    {128, 64, 1, 0.01f, 0.175f, 0.251f, 3.22f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 2, 1, 4>},
-    {64, 32, 2, 1.01f, 0.130f, 0.115f, 2.16f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 1, 1, 1, 6>},
-    {128, 128, 1, 4.18f, 0.391f, 0.371f, 0.05f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 2, 2, 3>},
-    {64, 64, 3, 1.16f, 0.222f, 0.182f, 1.48f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 1, 1, 3>},
+    {64, 32, 2, 1.00f, 0.131f, 0.116f, 1.50f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 1, 1, 1, 6>},
+    {64, 64, 1, 1.97f, 0.156f, 0.166f, 0.83f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 1, 1, 4>},
+    {64, 64, 3, 1.05f, 0.224f, 0.185f, 1.58f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 1, 1, 3>},
+    {128, 64, 1, 0.05f, 0.249f, 0.092f, 2.94f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 2, 1, 4>},
+    {128, 128, 1, 1.48f, 0.439f, 0.375f, 2.85f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 2, 2, 3>},
 };
 
 template <int NSH>
@@ -775,5 +926,6 @@ hipError_t gemm(const GemmCall& g, hipStream_t st) {
     default: return pick_shape(kHeadShapes, M, g.N, g.K, 1).launch(g, st);
   }
 }
+#endif
 
 }  // namespace atspeed

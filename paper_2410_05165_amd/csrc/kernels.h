@@ -21,7 +21,7 @@ struct GemmCall {
   void* hout;                // GU output [M, f]
   void* q; void* kdst; void* vdst;
   const float* cosT; const float* sinT;   // fp32 path: [max_pos, d_head/2] each
-  const float* ropeT;        // bf16 path: [max_pos][16][4] (cos, sin) of rotary index 16*b + i at [pos][i][b] (0 past d_head/2)
+  const float* ropeT;        // bf16 path: [max_pos][d_head/2] (cos, sin)
   Rows rows;
   int kv_mode, Pmax, d, dh, H;
 };

@@ -352,7 +352,7 @@ void layout(atspeed_ctx& c, const atspeed_config& cfg, int trie_nodes, Arena& a)
     const int half = m.d_model / m.n_heads / 2;
     r.cosT = a.take<float>((size_t)c.max_pos * half);
     r.sinT = a.take<float>((size_t)c.max_pos * half);
-    r.ropeT = a.take<float>((size_t)c.max_pos * 16 * 4 * 2);
+    r.ropeT = a.take<float>((size_t)c.max_pos * half * 2);
     r.lp = a.take<float>((size_t)B * Tm * c.nitem);
     r.root = a.take<float>((size_t)B * c.nitem);
     if (keep) {
@@ -459,17 +459,13 @@ atspeed_status upload_rope(atspeed_ctx& c, ModelRt& r) {
       cs[(size_t)p * half + i] = (float)std::cos(ang);
       sn[(size_t)p * half + i] = (float)std::sin(ang);
     }
-  // the same values regrouped for the bf16 q/k/v epilogue: (cos, sin) of rotary
-  // index 16*b + i at [pos][i][b], so a lane's four blocks are two 16-byte loads
-  std::vector<float> rt((size_t)c.max_pos * 16 * 4 * 2, 0.f);
-  for (int p = 0; p < c.max_pos; ++p)
-    for (int i = 0; i < 16; ++i)
-      for (int b = 0; b < 4; ++b) {
-        const int ri = 16 * b + i;
-        if (ri >= half) continue;
-        rt[(((size_t)p * 16 + i) * 4 + b) * 2] = cs[(size_t)p * half + ri];
-        rt[(((size_t)p * 16 + i) * 4 + b) * 2 + 1] = sn[(size_t)p * half + ri];
-      }
+  // the same values as (cos, sin) pairs for the bf16 q/k/v epilogue: a lane's
+  // four consecutive rotary indices are two 16-byte loads
+  std::vector<float> rt((size_t)c.max_pos * half * 2);
+  for (size_t i = 0; i < (size_t)c.max_pos * half; ++i) {
+    rt[2 * i] = cs[i];
+    rt[2 * i + 1] = sn[i];
+  }
   HIP_TRY(hipMemcpyAsync(r.cosT, cs.data(), cs.size() * 4, hipMemcpyHostToDevice, c.st));
   HIP_TRY(hipMemcpyAsync(r.sinT, sn.data(), sn.size() * 4, hipMemcpyHostToDevice, c.st));
   HIP_TRY(hipMemcpyAsync(r.ropeT, rt.data(), rt.size() * 4, hipMemcpyHostToDevice, c.st));
