@@ -849,54 +849,55 @@ struct Shape {
   hipError_t (*launch)(const GemmCall&, hipStream_t);
 };
 const Shape kQkvShapes[] = {
-    {32, 64, 2, 2.72f, 0.214f, 0.169f, 1.36f, launch_bf16<BMAP_QKV, EPI_QKV, 1, 2, 1, 1, 6>},
-    {64, 64, 2, 2.43f, 0.245f, 0.172f, 1.40f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 1, 1, 4>},
-    {64, 64, 3, 3.22f, 0.280f, 0.213f, 0.44f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 1, 1, 3>},
-    {128, 64, 1, 1.51f, 0.329f, 0.021f, 2.42f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 1, 1, 4>},
-    {64, 256, 1, 2.29f, 0.612f, 0.076f, 3.12f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 4, 1, 2, 3>},
-    {128, 128, 1, 1.18f, 0.502f, 0.502f, 4.50f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 1, 2, 4>},
-    {128, 128, 2, 3.59f, 0.731f, 0.479f, 2.33f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 2, 2, 2>},
-    {128, 256, 1, 2.27f, 0.794f, 0.536f, 6.46f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 2, 4, 2>},
-    {256, 128, 1, 0.00f, 0.777f, 0.515f, 9.70f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 4, 2, 2>},
-    {192, 192, 1, 0.55f, 0.847f, 0.616f, 9.79f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 3, 3, 2>},
-    {192, 256, 1, 0.00f, 0.998f, 0.309f, 11.65f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 3, 4, 2>},
-    {256, 256, 1, 1.12f, 1.379f, 0.562f, 9.45f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 2, 4, 2>},
+    {32, 64, 2, 2.77f, 0.239f, 0.173f, 1.18f, launch_bf16<BMAP_QKV, EPI_QKV, 1, 2, 1, 1, 6>},
+    {64, 64, 2, 2.49f, 0.268f, 0.204f, 1.23f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 1, 1, 4>},
+    {64, 64, 3, 3.37f, 0.308f, 0.233f, 0.18f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 1, 1, 3>},
+    {128, 64, 1, 1.68f, 0.339f, 0.049f, 2.40f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 1, 1, 4>},
+    {64, 256, 1, 2.68f, 0.614f, 0.296f, 2.75f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 4, 1, 2, 3>},
+    {128, 128, 1, 1.31f, 0.165f, 0.502f, 4.38f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 1, 2, 4>},
+    {128, 128, 2, 4.05f, 0.754f, 0.505f, 1.83f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 2, 2, 2>},
+    {128, 256, 1, 2.48f, 0.832f, 0.446f, 6.31f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 2, 4, 2>},
+    {256, 128, 1, 0.00f, 0.775f, 0.755f, 11.42f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 4, 2, 2>},
+    {192, 192, 1, 0.08f, 0.842f, 0.548f, 10.29f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 3, 3, 2>},
+    {192, 256, 1, 0.00f, 1.063f, 0.098f, 11.64f, launch_bf16<BMAP_QKV, EPI_QKV, 2, 2, 3, 4, 2>},
+    {256, 256, 1, 0.61f, 1.371f, 0.795f, 10.08f, launch_bf16<BMAP_QKV, EPI_QKV, 4, 2, 2, 4, 2>},
 };
 const Shape kGuShapes[] = {
-    {64, 64, 2, 2.22f, 0.305f, 0.224f, 0.91f, launch_bf16<BMAP_GU, EPI_GU, 2, 1, 1, 2, 4>},
-    {64, 128, 2, 1.69f, 0.454f, 0.316f, 1.27f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 1, 2, 3>},
-    {128, 64, 1, 1.61f, 0.340f, 0.226f, 1.90f, launch_bf16<BMAP_GU, EPI_GU, 4, 1, 1, 2, 4>},
-    {128, 128, 1, 1.41f, 0.132f, 0.518f, 3.02f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 2, 2, 4>},
-    {128, 128, 1, 1.54f, 0.546f, 0.548f, 2.18f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 1, 2, 3>},
-    {128, 128, 2, 2.34f, 0.719f, 0.507f, 1.92f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 2, 2, 2>},
-    {192, 128, 1, 0.00f, 0.705f, 0.215f, 5.35f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 3, 2, 4>},
-    {128, 256, 1, 0.00f, 0.903f, 0.770f, 6.11f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 1, 4, 3>},
-    {256, 128, 1, 0.00f, 0.803f, 0.830f, 4.96f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 2, 2, 3>},
-    {192, 256, 1, 0.00f, 1.048f, 0.620f, 7.95f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 3, 4, 2>},
-    {256, 256, 1, 0.00f, 1.319f, 0.513f, 10.58f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 4, 4, 2>},
-    {256, 256, 1, 0.00f, 1.464f, 0.505f, 7.44f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 2, 4, 2>},
+    {64, 64, 2, 2.61f, 0.307f, 0.238f, 0.50f, launch_bf16<BMAP_GU, EPI_GU, 2, 1, 1, 2, 4>},
+    {64, 128, 1, 2.37f, 0.402f, 0.374f, 0.80f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 1, 2, 4>},
+    {64, 128, 2, 1.65f, 0.493f, 0.317f, 1.16f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 1, 2, 3>},
+    {128, 64, 1, 1.67f, 0.388f, 0.042f, 1.68f, launch_bf16<BMAP_GU, EPI_GU, 4, 1, 1, 2, 4>},
+    {128, 128, 1, 1.82f, 0.530f, 0.405f, 2.60f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 2, 2, 4>},
+    {128, 128, 1, 1.84f, 0.559f, 0.436f, 1.84f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 1, 2, 3>},
+    {128, 128, 2, 2.51f, 0.790f, 0.509f, 1.90f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 2, 2, 2>},
+    {192, 128, 1, 0.00f, 0.738f, 0.399f, 5.33f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 3, 2, 4>},
+    {128, 256, 1, 0.00f, 0.904f, 0.046f, 6.57f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 1, 4, 3>},
+    {256, 128, 1, 0.00f, 0.806f, 0.154f, 5.24f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 2, 2, 3>},
+    {192, 256, 1, 0.00f, 1.050f, 0.901f, 8.69f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 3, 4, 2>},
+    {256, 256, 1, 0.00f, 1.204f, 1.320f, 10.15f, launch_bf16<BMAP_GU, EPI_GU, 2, 2, 4, 4, 2>},
+    {256, 256, 1, 0.00f, 1.462f, 1.044f, 7.46f, launch_bf16<BMAP_GU, EPI_GU, 4, 2, 2, 4, 2>},
 };
 const Shape kResidShapes[] = {
-    {64, 32, 2, 0.99f, 0.176f, 0.153f, 1.70f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 1, 1, 1, 6>},
-    {64, 64, 1, 1.84f, 0.172f, 0.227f, 0.61f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 1, 1, 4>},
-    {64, 64, 2, 1.87f, 0.250f, 0.212f, 0.83f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 1, 1, 3>},
-    {64, 128, 1, 0.64f, 0.361f, 0.032f, 2.52f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 1, 2, 4>},
-    {128, 64, 1, 0.18f, 0.336f, 0.042f, 2.63f, launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 2, 1, 1, 4>},
-    {128, 128, 1, 0.00f, 0.204f, 0.513f, 3.95f, launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 2, 1, 2, 4>},
-    {128, 128, 1, 0.00f, 0.494f, 0.268f, 4.29f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 2, 2, 3>},
-    {128, 128, 2, 1.05f, 0.716f, 0.540f, 3.21f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 2, 2, 2>},
-    {128, 256, 1, 0.00f, 0.853f, 0.065f, 6.38f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 2, 4, 2>},
-    {256, 128, 1, 0.00f, 0.826f, 0.749f, 7.28f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 4, 2, 2>},
-    {192, 256, 1, 0.00f, 1.052f, 0.123f, 9.08f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 3, 4, 2>},
-    {256, 256, 1, 0.00f, 1.385f, 0.348f, 10.60f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 4, 4, 2>},
+    {64, 32, 2, 1.09f, 0.195f, 0.160f, 1.51f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 1, 1, 1, 6>},
+    {64, 64, 1, 2.23f, 0.014f, 0.221f, 0.48f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 1, 1, 4>},
+    {64, 64, 2, 1.96f, 0.269f, 0.197f, 0.66f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 1, 1, 3>},
+    {64, 128, 1, 1.06f, 0.362f, 0.007f, 2.01f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 1, 2, 4>},
+    {128, 64, 1, 0.40f, 0.351f, 0.297f, 2.73f, launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 2, 1, 1, 4>},
+    {128, 128, 1, 0.00f, 0.527f, 0.237f, 4.91f, launch_bf16<BMAP_PLAIN, EPI_RESID, 4, 2, 1, 2, 4>},
+    {128, 128, 1, 0.42f, 0.161f, 0.550f, 3.50f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 2, 2, 3>},
+    {128, 128, 2, 1.49f, 0.747f, 0.533f, 2.71f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 2, 2, 2>},
+    {128, 256, 1, 0.00f, 0.860f, 0.547f, 6.35f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 2, 4, 2>},
+    {256, 128, 1, 0.00f, 0.831f, 0.736f, 7.36f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 4, 2, 2>},
+    {192, 256, 1, 0.00f, 1.061f, 0.378f, 9.12f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 3, 4, 2>},
+    {256, 256, 1, 0.00f, 1.391f, 0.316f, 10.91f, launch_bf16<BMAP_PLAIN, EPI_RESID, 2, 2, 4, 4, 2>},
 };
 // the item rows of the output head (at most 1,024 columns)
 const Shape kHeadShapes[] = {
-    {64, 32, 2, 1.00f, 0.131f, 0.116f, 1.50f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 1, 1, 1, 6>},
-    {64, 64, 1, 1.97f, 0.156f, 0.166f, 0.83f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 1, 1, 4>},
-    {64, 64, 3, 1.05f, 0.224f, 0.185f, 1.58f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 1, 1, 3>},
-    {128, 64, 1, 0.05f, 0.249f, 0.092f, 2.94f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 2, 1, 4>},
-    {128, 128, 1, 1.48f, 0.439f, 0.375f, 2.85f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 2, 2, 3>},
+    {64, 32, 2, 0.99f, 0.130f, 0.115f, 1.82f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 1, 1, 1, 6>},
+    {64, 64, 1, 1.96f, 0.012f, 0.166f, 0.74f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 1, 1, 4>},
+    {64, 64, 3, 1.03f, 0.226f, 0.183f, 1.60f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 1, 1, 3>},
+    {128, 64, 1, 0.00f, 0.202f, 0.250f, 2.97f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 2, 1, 4>},
+    {128, 128, 1, 1.51f, 0.435f, 0.340f, 2.85f, launch_bf16<BMAP_PLAIN, EPI_STORE, 2, 2, 2, 2, 3>},
 };
 
 template <int NSH>

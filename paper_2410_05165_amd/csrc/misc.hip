@@ -1,19 +1,8 @@
-// Row-wise kernels of the forward: embedding gather, RMSNorm, item log-softmax.
+// Row-wise kernels of the forward: embedding gather with the first RMSNorm, RMSNorm, item log-softmax.
 #include "common.h"
 #include "kernels.h"
 
 namespace atspeed {
-
-template <class T>
-__global__ void embed_kernel(const T* __restrict__ emb, const int* __restrict__ tok, const int* __restrict__ Mdev,
-                             int d, float* __restrict__ x) {
-  const int M = *Mdev;
-  const size_t total = (size_t)M * d;
-  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
-    const size_t r = i / d, c = i % d;
-    x[i] = St<T>::ld(emb + (size_t)tok[r] * d + c);
-  }
-}
 
 // Copy of the k and v rows a forward wrote, in row order (instrumentation of
 // the residual capture): row r's k/v sit in the prefix cache [B][H][Pmax][dh]
@@ -40,14 +29,6 @@ hipError_t gather_kv_rows(const void* kc, const void* vc, const Rows& rows, int 
   return hipGetLastError();
 }
 
-hipError_t embed(bool bf16, const void* emb, const Rows& rows, int Mmax, int d, float* x, hipStream_t st) {
-  int blocks = (int)std::min<size_t>(4096, ((size_t)Mmax * d + 255) / 256);
-  if (blocks < 1) blocks = 1;
-  if (bf16) hipLaunchKernelGGL(embed_kernel<bf16_t>, dim3(blocks), dim3(256), 0, st, (const bf16_t*)emb, rows.token, rows.M, d, x);
-  else hipLaunchKernelGGL(embed_kernel<float>, dim3(blocks), dim3(256), 0, st, (const float*)emb, rows.token, rows.M, d, x);
-  return hipGetLastError();
-}
-
 __device__ __forceinline__ float block_sum256(float v, float* red) {
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
   const int w = threadIdx.x >> 6;
@@ -69,7 +50,9 @@ __device__ __forceinline__ float block_max256(float v, float* red) {
 // out[r] = g * x[src] / sqrt(mean(x[src]^2) + eps), src = row_index ? row_index[r] : r.
 // With add: x[src] + add[src] takes the place of x[src] (the second partial
 // product of a GEMM split in k), and without row_index that sum is written
-// back to x.  One workgroup per row; the row is read once in 16-byte loads and
+// back to x.  With EMB the row is the embedding of tok[r] instead, and x[r] is
+// written too (the first norm of a forward: the gather alone took 28 us at 2,624 x
+// 4,096 and 63 at 7,744, and the norm read it back).  One workgroup per row; the row is read once in 16-byte loads and
 // held in registers (up to 256 * 4 * VMAX columns) between the sum of squares
 // and the scaled write.
 constexpr int kNormVmax = 8;
@@ -88,23 +71,33 @@ __device__ __forceinline__ void store4<bf16_t>(bf16_t* p, float a, float b, floa
   *reinterpret_cast<uint2*>(p) = w;
 }
 
-template <class T>
+// Four consecutive stored values (aligned to their size) as floats.
+__device__ __forceinline__ float4 load4(const float* p) { return *reinterpret_cast<const float4*>(p); }
+__device__ __forceinline__ float4 load4(const bf16_t* p) {
+  const uint2 w = *reinterpret_cast<const uint2*>(p);
+  return make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
+                     __uint_as_float(w.y & 0xffff0000u));
+}
+
+template <class T, bool EMB>
 __global__ void __launch_bounds__(256)
 rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ add, const int* __restrict__ Mdev, int d,
-               const float* __restrict__ g, T* __restrict__ out, const int* __restrict__ row_index) {
+               const float* __restrict__ g, T* __restrict__ out, const int* __restrict__ row_index,
+               const T* __restrict__ emb, const int* __restrict__ tok) {
   __shared__ float red[4];
   const int M = *Mdev;
   const int n4 = d >> 2;
   for (int r = blockIdx.x; r < M; r += gridDim.x) {
     const int src = row_index ? row_index[r] : r;
     const float4* xr = reinterpret_cast<const float4*>(x + (size_t)src * d);  // read once, before any write-back
+    const T* er = EMB ? emb + (size_t)tok[r] * d : nullptr;
     // every load of the row is issued before any store (the x write-back waits
     // until after the reduction): 18.1 -> 17.0 us at 1,920 x 4,096, same bits
     float4 v[kNormVmax], p[kNormVmax];
 #pragma unroll
     for (int k = 0; k < kNormVmax; ++k) {
       const int c = threadIdx.x + k * 256;
-      v[k] = c < n4 ? xr[c] : make_float4(0.f, 0.f, 0.f, 0.f);
+      v[k] = c < n4 ? (EMB ? load4(er + 4 * c) : xr[c]) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
     if (add) {
 #pragma unroll
@@ -128,7 +121,7 @@ rmsnorm_kernel(float* __restrict__ x, const float* __restrict__ add, const int* 
     for (int k = 0; k < kNormVmax; ++k) {
       const int c = threadIdx.x + k * 256;
       if (c < n4) {
-        if (add && !row_index) reinterpret_cast<float4*>(x + (size_t)src * d)[c] = v[k];
+        if (EMB || (add && !row_index)) reinterpret_cast<float4*>(x + (size_t)src * d)[c] = v[k];
         const float4 gg = g4[c];
         store4<T>(out + (size_t)r * d + 4 * c, v[k].x * inv * gg.x, v[k].y * inv * gg.y, v[k].z * inv * gg.z,
                   v[k].w * inv * gg.w);
@@ -142,9 +135,24 @@ hipError_t rmsnorm(bool bf16, float* x, const float* add, const int* Mdev, int M
   if (d % 4 != 0 || d > 1024 * kNormVmax) return hipErrorInvalidValue;
   int blocks = std::max(1, std::min(Mmax, 8192));
   if (bf16)
-    hipLaunchKernelGGL(rmsnorm_kernel<bf16_t>, dim3(blocks), dim3(256), 0, st, x, add, Mdev, d, g, (bf16_t*)out, row_index);
+    hipLaunchKernelGGL((rmsnorm_kernel<bf16_t, false>), dim3(blocks), dim3(256), 0, st, x, add, Mdev, d, g, (bf16_t*)out,
+                       row_index, (const bf16_t*)nullptr, (const int*)nullptr);
   else
-    hipLaunchKernelGGL(rmsnorm_kernel<float>, dim3(blocks), dim3(256), 0, st, x, add, Mdev, d, g, (float*)out, row_index);
+    hipLaunchKernelGGL((rmsnorm_kernel<float, false>), dim3(blocks), dim3(256), 0, st, x, add, Mdev, d, g, (float*)out,
+                       row_index, (const float*)nullptr, (const int*)nullptr);
+  return hipGetLastError();
+}
+
+hipError_t embed_norm(bool bf16, const void* emb, const Rows& rows, int Mmax, int d, const float* g, float* x, void* out,
+                      hipStream_t st) {
+  if (d % 4 != 0 || d > 1024 * kNormVmax) return hipErrorInvalidValue;
+  const int blocks = std::max(1, std::min(Mmax, 8192));
+  if (bf16)
+    hipLaunchKernelGGL((rmsnorm_kernel<bf16_t, true>), dim3(blocks), dim3(256), 0, st, x, (const float*)nullptr, rows.M, d,
+                       g, (bf16_t*)out, (const int*)nullptr, (const bf16_t*)emb, rows.token);
+  else
+    hipLaunchKernelGGL((rmsnorm_kernel<float, true>), dim3(blocks), dim3(256), 0, st, x, (const float*)nullptr, rows.M, d,
+                       g, (float*)out, (const int*)nullptr, (const float*)emb, rows.token);
   return hipGetLastError();
 }
 

@@ -103,7 +103,6 @@ struct atspeed_ctx {
   void* h = nullptr;
   float* logits = nullptr;
   float* part = nullptr;      // bf16: second k-half of the o / down product [Mmax, d] fp32
-  int* lo = nullptr;
   int* hi = nullptr;
   int* lvl_lo = nullptr;
   int* lvl_hi = nullptr;
@@ -121,6 +120,7 @@ struct atspeed_ctx {
   int B = 0, P = 0;
   bool prefilled = false;
   bool drafted = false;
+  bool at_root = false;        // no user has left item level 0 since the prefill: the tree of paths is empty
   // tree-KV reuse (cfg.reuse_tree_kv): the target's per-layer tree K/V and its
   // log-probs by slot live in two buffer sets that alternate between verifies;
   // a verify of the decode loop takes the nodes the previous one already
@@ -375,7 +375,11 @@ void layout(atspeed_ctx& c, const atspeed_config& cfg, int trie_nodes, Arena& a)
   c.h = a.take<char>(M * fmax * es);
   c.logits = a.take<float>(M * c.nitem);
   c.part = c.bf16 ? a.take<float>(M * dmax) : nullptr;
-  c.rows.M = a.take<int>(1);
+  // the validity word, the row count and the largest per-user row count of a tree
+  // plan side by side: one read-back fetches them
+  c.err = a.take<int>(3);
+  c.rows.M = c.err ? c.err + 1 : nullptr;
+  c.plan_max = c.err ? c.err + 2 : nullptr;
   c.rows.user = a.take<int>(M);
   c.rows.token = a.take<int>(M);
   c.rows.pos = a.take<int>(M);
@@ -405,15 +409,12 @@ void layout(atspeed_ctx& c, const atspeed_config& cfg, int trie_nodes, Arena& a)
   c.tree.q_score = a.take<float>((size_t)B * Tm);
   c.tree.tpath = a.take<uint32_t>((size_t)B * Tm);
   c.tree.ttrie = a.take<int>((size_t)B * Tm);
-  c.lo = a.take<int>(B);
   c.hi = a.take<int>(B);
   c.lvl_lo = a.take<int>(B);
   c.lvl_hi = a.take<int>(B);
   c.row_last = a.take<int>(B);
   c.Mb = a.take<int>(1);
   c.Mall = a.take<int>(1);
-  c.plan_max = a.take<int>(1);
-  c.err = a.take<int>(1);
   c.acc_tmp = a.take<int>(B);
   c.tafter_tmp = a.take<int>(B);
   c.keys = a.take<unsigned long long>((size_t)B * c.max_cand);
@@ -517,8 +518,6 @@ atspeed_status forward(atspeed_ctx& c, ModelRt& r, bool prefill, int Mmax, int T
                              hipMemcpyDeviceToDevice, st));
     HIP_TRY(hipMemcpyAsync(c.cap_plan + (size_t)3 * c.cap_rows, c.rows.M, sizeof(int), hipMemcpyDeviceToDevice, st));
   }
-  MARK(ATSPEED_K_ROW);
-  HIP_TRY(embed(c.bf16, r.emb, c.rows, Mmax, d, c.x, st));
   // bf16: the o and down projections split k at its midpoint (whole even
   // numbers of 64-column k-tiles), so 256x256 tiles fill the CUs at these
   // widths; the first half adds into x, the second goes to c.part, and the
@@ -529,8 +528,8 @@ atspeed_status forward(atspeed_ctx& c, ModelRt& r, bool prefill, int Mmax, int T
   for (int l = 0; l < m.n_layers; ++l) {
     const void* const* w = &r.layers[(size_t)l * 9];
     MARK(ATSPEED_K_ROW);
-    HIP_TRY(rmsnorm(c.bf16, c.x, l > 0 ? part_down : nullptr, c.rows.M, Mmax, d, (const float*)w[0], c.xn, nullptr,
-                    st));
+    if (l == 0) HIP_TRY(embed_norm(c.bf16, r.emb, c.rows, Mmax, d, (const float*)w[0], c.x, c.xn, st));
+    else HIP_TRY(rmsnorm(c.bf16, c.x, part_down, c.rows.M, Mmax, d, (const float*)w[0], c.xn, nullptr, st));
     if (cap) HIP_TRY(capture(2 * l));       // the layer's input (the previous k-split half added)
     if (cap_act) HIP_TRY(capture_act(l, 0, c.xn, d));
     GemmCall g{};
@@ -618,7 +617,6 @@ atspeed_status read_err(atspeed_ctx& c, int* out) {
 // verify of the loop forwarded (with tree-KV reuse configured).
 atspeed_status tree_forward(atspeed_ctx& c, float* dbg_logits, bool carry = false) {
   HIP_TRY(hipMemsetAsync(c.err, 0, sizeof(int), c.st));
-  HIP_TRY(hipMemsetAsync(c.lo, 0, sizeof(int) * c.B, c.st));
   MARK(ATSPEED_K_SELECT);
   launch_tree_index(c.tree, c.trie, c.state, c.B, c.cfg.target.item_base, c.cfg.codebook, c.cfg.L, c.err, c.st);
   HIP_TRY(hipGetLastError());
@@ -629,18 +627,16 @@ atspeed_status tree_forward(atspeed_ctx& c, float* dbg_logits, bool carry = fals
     launch_carry_match(c.tree, c.state, c.prev_tpath, c.prev_depth, use_prev ? c.prev_n : nullptr, c.src, c.fidx,
                        c.fcnt, c.B, c.st);
     HIP_TRY(hipGetLastError());
-    launch_plan_tree(c.tree, c.lo, c.fcnt, c.B, c.P, c.rows, c.plan_max, c.st, c.fidx);
+    launch_plan_tree(c.tree, nullptr, c.fcnt, c.B, c.P, c.rows, c.plan_max, c.st, c.fidx);
   } else {
-    launch_plan_tree(c.tree, c.lo, c.state.nfwd, c.B, c.P, c.rows, c.plan_max, c.st);
+    launch_plan_tree(c.tree, nullptr, c.state.nfwd, c.B, c.P, c.rows, c.plan_max, c.st);
   }
   HIP_TRY(hipGetLastError());
   // One read-back per forward: the validity word, the row count and the largest
   // per-user row count, so a malformed tree never reaches the forward and every
   // launch of the forward is sized to the rows it has.
   int info[3] = {0, 0, 0};
-  HIP_TRY(hipMemcpyAsync(&info[0], c.err, sizeof(int), hipMemcpyDeviceToHost, c.st));
-  HIP_TRY(hipMemcpyAsync(&info[1], c.rows.M, sizeof(int), hipMemcpyDeviceToHost, c.st));
-  HIP_TRY(hipMemcpyAsync(&info[2], c.plan_max, sizeof(int), hipMemcpyDeviceToHost, c.st));
+  HIP_TRY(hipMemcpyAsync(info, c.err, sizeof(info), hipMemcpyDeviceToHost, c.st));
   HIP_TRY(hipStreamSynchronize(c.st));
   if (info[0]) return fail(ATSPEED_E_INVALID, "malformed tree (code " + std::to_string(info[0]) + ")");
   if (c.reuse) {
@@ -808,6 +804,7 @@ static atspeed_status prefill_impl(atspeed_ctx* c, int32_t B, int32_t P, const i
   HIP_TRY(hipMemsetAsync(c->tree.n_nodes, 0, sizeof(int) * B, c->st));
   HIP_TRY(hipStreamSynchronize(c->st));  // host vectors above go out of scope
   c->prefilled = true;
+  c->at_root = true;
   c->dft_prefilled = with_draft && c->dft.present;
   c->drafted = false;
   c->carry_ok = false;
@@ -828,10 +825,14 @@ atspeed_status atspeed_draft(atspeed_ctx* c) {
   const int B = c->B, L = cf.L;
   launch_tree_from_beams(c->state, c->tree, c->trie, B, cf.target.item_base, cf.codebook, L, c->st);
   HIP_TRY(hipGetLastError());
-  // draft log-probs along the Y_t paths (none at t = 0), then the beams' draft scores
-  HIP_TRY(hipMemsetAsync(c->lo, 0, sizeof(int) * B, c->st));
-  launch_plan_tree(c->tree, c->lo, c->state.npath, B, c->P, c->rows, nullptr, c->st);
-  HIP_TRY(hipGetLastError());
+  // draft log-probs along the Y_t paths, then the beams' draft scores.  At t = 0
+  // there are no paths and the forward would be launches over no rows (0.1 ms for
+  // four layers); an armed capture of the draft still counts it.
+  const bool paths = !c->at_root || (c->cap_x != nullptr && c->cap_model == 1);
+  if (paths) {
+    launch_plan_tree(c->tree, nullptr, c->state.npath, B, c->P, c->rows, nullptr, c->st);
+    HIP_TRY(hipGetLastError());
+  }
   // Row bounds of the draft forwards (the row counts themselves stay on the
   // device): the Y_t paths are prefixes of at most K beams at depths 1..t < L,
   // and a drafted level holds at most N nodes per user (the strict and the
@@ -840,7 +841,7 @@ atspeed_status atspeed_draft(atspeed_ctx* c) {
   // choose the GEMM tiles, so they are kept tight.
   c->align_ready = false;  // the tree is rebuilt below
   const int path_rows = std::max(1, cf.K * (L - 1)), level_rows = std::max(1, cf.N);
-  ST_TRY(forward(*c, c->dft, false, B * path_rows, path_rows, nullptr));
+  if (paths) ST_TRY(forward(*c, c->dft, false, B * path_rows, path_rows, nullptr));
   launch_draft_beam_scores(c->state, c->tree, c->dft.lp, c->dft.root, c->nitem, cf.codebook, L, B, c->st);
   HIP_TRY(hipGetLastError());
   for (int j = 1; j <= std::min(cf.gamma, L); ++j) {
@@ -883,6 +884,7 @@ atspeed_status atspeed_tree_logits(atspeed_ctx* c, float* logits) {
 static atspeed_status accept_on(atspeed_ctx* c, const float* lpt, const float* roott, int32_t* accepted,
                                 int32_t* t_after) {
   const atspeed_config& cf = c->cfg;
+  c->at_root = false;
   HIP_TRY(mark(*c, ATSPEED_K_SELECT));
   if (cf.mode == ATSPEED_STRICT) {
     launch_verify_strict(c->state, c->tree, c->trie, lpt, roott, c->nitem, cf.codebook, cf.L, c->keys, c->max_cand,
@@ -966,6 +968,7 @@ atspeed_status atspeed_accept_noalloc(atspeed_ctx* c, const float* logits, const
   HIP_TRY(log_softmax_rows(root_logits, c->Mb, c->B, c->nitem, nullptr, root, nullptr, c->st));
   int* acc = accepted ? accepted : c->acc_tmp;
   int* ta = t_after ? t_after : c->tafter_tmp;
+  c->at_root = false;
   if (!relaxed) {
     launch_verify_strict(c->state, c->tree, c->trie, lp, root, c->nitem, cf.codebook, cf.L, keys, c->max_cand, acc,
                          ta, c->B, c->st);
@@ -1037,6 +1040,7 @@ atspeed_status atspeed_set_state(atspeed_ctx* c, int32_t B, const int32_t* t, co
       tr[(size_t)u * K + k] = node;
     }
   }
+  c->at_root = false;
   HIP_TRY(hipMemcpyAsync(c->state.t, t, B * 4, hipMemcpyHostToDevice, c->st));
   HIP_TRY(hipMemcpyAsync(c->state.nb, nbeams, B * 4, hipMemcpyHostToDevice, c->st));
   HIP_TRY(hipMemcpyAsync(c->state.path, pk.data(), pk.size() * 4, hipMemcpyHostToDevice, c->st));
@@ -1123,6 +1127,7 @@ atspeed_status atspeed_target_search(atspeed_ctx* c, int32_t B, int32_t P, const
   ST_TRY(prefill_impl(c, B, P, prefix, nullptr, false));
   const atspeed_config& cf = c->cfg;
   const int L = cf.L;
+  c->at_root = false;   // the searches advance the users' levels
   if (step_n) HIP_TRY(hipMemsetAsync(step_n, 0, sizeof(int) * B, c->st));
   for (int l = 0; l < L; ++l) {
     // the tree of the Y_t paths alone: the verify has no drafted level, so it
@@ -1205,15 +1210,12 @@ atspeed_status atspeed_align_step(atspeed_ctx* c, const atspeed_align_args* a, d
   // the context rows: every tree node of depth < L (the leaves of depth L are
   // labels only)
   HIP_TRY(hipMemsetAsync(c->err, 0, sizeof(int), c->st));
-  HIP_TRY(hipMemsetAsync(c->lo, 0, sizeof(int) * B, c->st));
   launch_tree_index(c->tree, c->trie, c->state, B, cf.target.item_base, cf.codebook, L, c->err, c->st);
   HIP_TRY(hipGetLastError());
-  launch_plan_tree(c->tree, c->lo, c->state.nfwd, B, c->P, c->rows, c->plan_max, c->st);
+  launch_plan_tree(c->tree, nullptr, c->state.nfwd, B, c->P, c->rows, c->plan_max, c->st);
   HIP_TRY(hipGetLastError());
   int info[3] = {0, 0, 0};
-  HIP_TRY(hipMemcpyAsync(&info[0], c->err, sizeof(int), hipMemcpyDeviceToHost, c->st));
-  HIP_TRY(hipMemcpyAsync(&info[1], c->rows.M, sizeof(int), hipMemcpyDeviceToHost, c->st));
-  HIP_TRY(hipMemcpyAsync(&info[2], c->plan_max, sizeof(int), hipMemcpyDeviceToHost, c->st));
+  HIP_TRY(hipMemcpyAsync(info, c->err, sizeof(info), hipMemcpyDeviceToHost, c->st));
   HIP_TRY(hipStreamSynchronize(c->st));
   if (info[0]) return fail(ATSPEED_E_INVALID, "align_step: the context tree is malformed (code " + std::to_string(info[0]) + ")");
   const int M = info[1];
@@ -1256,14 +1258,14 @@ atspeed_status atspeed_mixed_search(atspeed_ctx* c, float lambda, int32_t B, int
   ST_TRY(prefill_impl(c, B, P, prefix, nullptr, true));
   const atspeed_config& cf = c->cfg;
   const int L = cf.L, path_rows = std::max(1, cf.K * (L - 1));
+  c->at_root = false;
   if (step_n) HIP_TRY(hipMemsetAsync(step_n, 0, sizeof(int) * B, c->st));
   for (int l = 0; l < L; ++l) {
     // the Y_t paths alone, through the target and the draft
     launch_tree_from_beams(c->state, c->tree, c->trie, B, cf.target.item_base, cf.codebook, L, c->st);
     HIP_TRY(hipGetLastError());
     ST_TRY(tree_forward(*c, nullptr, true));
-    HIP_TRY(hipMemsetAsync(c->lo, 0, sizeof(int) * B, c->st));
-    launch_plan_tree(c->tree, c->lo, c->state.npath, B, c->P, c->rows, nullptr, c->st);
+      launch_plan_tree(c->tree, nullptr, c->state.npath, B, c->P, c->rows, nullptr, c->st);
     HIP_TRY(hipGetLastError());
     ST_TRY(forward(*c, c->dft, false, B * path_rows, path_rows, nullptr));
     // the mixture into the draft's rows, then the strict TopK of the next level

@@ -8,6 +8,7 @@
 // sequence (the pinned tie-break).  Keys are unique because paths are.
 // TopK is a radix select on those keys (8 bits per pass, 256-bin LDS histogram)
 // followed by a rank sort of the K survivors, one workgroup per user.
+#include <algorithm>
 #include "common.h"
 #include "select.h"
 #include "select_dev.h"
@@ -70,38 +71,55 @@ __global__ void tree_from_beams_kernel(StateDev s, TreeDev tr, TrieDev trie, int
 }
 
 // Derived per-node data of a caller or draft tree: path key, trie node, ancestors;
-// validation; number of nodes to forward (depth < L, a prefix of the level order).
-__global__ void tree_index_kernel(TreeDev tr, TrieDev trie, StateDev s, int item_base, int codebook, int L, int* err) {
-  const int u = blockIdx.x;
-  const size_t tb = (size_t)u * tr.max_nodes;
-  const int n = s.t[u] >= L ? 0 : tr.n_nodes[u];
+// validation; number of nodes to forward (depth < L, a prefix of the level order);
+// and the slots of Y_t's beams, each of which must be a node of depth t.
+// A node's walk is a chain of dependent lookups, so the tree's own arrays are
+// staged in LDS first (up to kStaged nodes), leaving one trie lookup a level.
+__global__ void __launch_bounds__(256)
+tree_index_kernel(TreeDev tr, TrieDev trie, StateDev s, int item_base, int codebook, int L, int* err) {
+  constexpr int kStaged = 1024;
   __shared__ int nfwd, bad;
-  if (threadIdx.x == 0) {
+  __shared__ int dep_s[kStaged], par_s[kStaged], tok_s[kStaged];
+  __shared__ uint32_t path_s[kStaged];
+  const int u = blockIdx.x, tid = threadIdx.x;
+  const size_t tb = (size_t)u * tr.max_nodes;
+  const int t = s.t[u], n = t >= L ? 0 : tr.n_nodes[u];
+  if (tid == 0) {
     nfwd = n;
     bad = 0;
   }
-  __syncthreads();
   if (n < 0 || n > tr.max_nodes) {
-    if (threadIdx.x == 0) {
+    if (tid == 0) {
       atomicOr(err, 1);
       s.nfwd[u] = 0;   // nothing of this user is forwarded
     }
     return;
   }
-  for (int i = threadIdx.x; i < n; i += blockDim.x) {
-    int chain[4], dep = tr.depth[tb + i], cur = i, ok = dep >= 1 && dep <= L;
+  const bool staged = n <= kStaged;
+  if (staged)
+    for (int i = tid; i < n; i += 256) {
+      dep_s[i] = tr.depth[tb + i];
+      par_s[i] = tr.parent[tb + i];
+      tok_s[i] = tr.token[tb + i];
+    }
+  __syncthreads();
+  auto depth = [&](int i) { return staged ? dep_s[i] : tr.depth[tb + i]; };
+  auto parent = [&](int i) { return staged ? par_s[i] : tr.parent[tb + i]; };
+  auto token = [&](int i) { return staged ? tok_s[i] : tr.token[tb + i]; };
+  for (int i = tid; i < n; i += 256) {
+    int chain[4], dep = depth(i), cur = i, ok = dep >= 1 && dep <= L;
     for (int l = dep; ok && l >= 1; --l) {
-      if (cur < 0 || cur > i || tr.depth[tb + cur] != l) { ok = 0; break; }
+      if (cur < 0 || cur > i || depth(cur) != l) { ok = 0; break; }
       chain[l - 1] = cur;
-      const int p = tr.parent[tb + cur];
+      const int p = parent(cur);
       if (l == 1 ? p != -1 : (p < 0 || p >= cur)) { ok = 0; break; }
       cur = p;
     }
-    if (ok && i > 0 && tr.depth[tb + i - 1] > dep) ok = 0;  // level order
+    if (ok && i > 0 && depth(i - 1) > dep) ok = 0;  // level order
     uint32_t path = 0;
     int node = 0;
     for (int l = 1; ok && l <= dep; ++l) {
-      const int code = tr.token[tb + chain[l - 1]] - item_base - codebook * (l - 1);
+      const int code = token(chain[l - 1]) - item_base - codebook * (l - 1);
       if (code < 0 || code >= codebook) { ok = 0; break; }
       node = trie_child(trie, node, code);
       if (node < 0) { ok = 0; break; }
@@ -114,57 +132,73 @@ __global__ void tree_index_kernel(TreeDev tr, TrieDev trie, StateDev s, int item
     }
     tr.tpath[tb + i] = path;
     tr.ttrie[tb + i] = node;
+    if (staged) path_s[i] = path;
     if (dep == L) atomicMin(&nfwd, i);
   }
   __syncthreads();
   // A user whose tree has any malformed node forwards nothing: the row planner
   // walks parents, depths and tokens of the forwarded nodes, and only
   // validated ones keep those walks inside the tree and the tables.
-  if (threadIdx.x == 0) s.nfwd[u] = bad ? 0 : nfwd;
-}
-
-// Beam slots of Y_t in a caller tree (verify): every beam path must be a node of depth t.
-__global__ void find_beam_slots_kernel(TreeDev tr, StateDev s, int L, int* err) {
-  const int u = blockIdx.x;
-  const int t = s.t[u];
-  if (t <= 0 || t >= L) return;
-  const size_t tb = (size_t)u * tr.max_nodes;
-  const int n = tr.n_nodes[u];
-  if (n < 0 || n > tr.max_nodes) return;   // flagged by tree_index_kernel
-  for (int k = threadIdx.x; k < s.nb[u]; k += blockDim.x) {
+  if (tid == 0) s.nfwd[u] = bad ? 0 : nfwd;
+  if (t <= 0 || t >= L || bad) return;   // a malformed tree is reported as such
+  for (int k = tid; k < s.nb[u]; k += 256) {
     const uint32_t p = s.path[u * s.K + k];
     int found = -1;
     for (int i = 0; i < n; ++i)
-      if (tr.depth[tb + i] == t && tr.tpath[tb + i] == p) { found = i; break; }
+      if (depth(i) == t && (staged ? path_s[i] : tr.tpath[tb + i]) == p) { found = i; break; }
     if (found < 0) atomicOr(err, 2);
     s.beam_slot[u * s.K + k] = found;
   }
 }
 
-// Rows of one forward: nodes with slot in [lo[u], hi[u]) of every user, users in
-// order; with idx, entries [lo[u], hi[u]) of the user's node list idx instead.
-__global__ void plan_tree_rows_kernel(TreeDev tr, const int* lo, const int* hi, const int* idx, int B, int P,
-                                      Rows rows, int* maxrows) {
-  __shared__ int off[1025];
-  if (threadIdx.x == 0) {
-    int acc = 0, mx = 0;
-    for (int u = 0; u < B; ++u) {
-      off[u] = acc;
-      rows.user_off[u] = acc;
-      const int n = max(0, hi[u] - lo[u]);
-      acc += n;
-      mx = max(mx, n);
-    }
-    off[B] = acc;
-    rows.user_off[B] = acc;
-    *rows.M = acc;
-    if (maxrows) *maxrows = mx;
+// Rows of one forward: nodes with slot in [lo[u], hi[u]) of every user (lo null:
+// from 0), users in order; with idx, entries [lo[u], hi[u]) of the user's node list
+// idx instead.  Every workgroup computes the users' offsets for itself (at most
+// 1,024 of them) and plans its share of the rows; the first one publishes the
+// offsets and counts.
+__global__ void __launch_bounds__(256)
+plan_tree_rows_kernel(TreeDev tr, const int* lo, const int* hi, const int* idx, int B, int P, Rows rows, int* maxrows) {
+  __shared__ int off[1025], wsum[4], wmax[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // four users a thread, then a prefix sum over the threads
+  int n[4], sum = 0, mx = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int u = tid * 4 + j;
+    n[j] = u < B ? max(0, hi[u] - (lo ? lo[u] : 0)) : 0;
+    sum += n[j];
+    mx = max(mx, n[j]);
   }
+  int incl = sum;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int v = __shfl_up(incl, o);
+    if (lane >= o) incl += v;
+    mx = max(mx, __shfl_xor(mx, o));
+  }
+  if (lane == 63) wsum[wave] = incl;
+  if (lane == 0) wmax[wave] = mx;
   __syncthreads();
+  int before = incl - sum;
+  for (int w = 0; w < wave; ++w) before += wsum[w];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (tid * 4 + j <= B) off[tid * 4 + j] = before;
+    before += n[j];
+  }
+  const int total = wsum[0] + wsum[1] + wsum[2] + wsum[3];
+  if (tid == 0) off[B] = total;
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    for (int u = tid; u <= B; u += 256) rows.user_off[u] = off[u];
+    if (tid == 0) {
+      *rows.M = total;
+      if (maxrows) *maxrows = max(max(wmax[0], wmax[1]), max(wmax[2], wmax[3]));
+    }
+  }
   // every row in parallel: its user is the last u with off[u] <= r (users
   // without rows share their offset with the next one and are never picked)
-  const int total = off[B];
-  for (int r = threadIdx.x; r < total; r += blockDim.x) {
+  for (int r = blockIdx.x * 256 + tid; r < total; r += gridDim.x * 256) {
     int ul = 0, uh = B - 1;
     while (ul < uh) {
       const int mid = (ul + uh + 1) >> 1;
@@ -172,23 +206,21 @@ __global__ void plan_tree_rows_kernel(TreeDev tr, const int* lo, const int* hi, 
     }
     const int u = ul;
     const size_t tb = (size_t)u * tr.max_nodes;
-    {
-      const int e = lo[u] + (r - off[u]);
-      const int s = idx ? idx[tb + e] : e;
-      const int dep = tr.depth[tb + s];
-      rows.user[r] = u;
-      rows.token[r] = tr.token[tb + s];
-      rows.pos[r] = P + dep - 1;
-      rows.slot[r] = (int)(tb + s);
-      rows.nctx[r] = P;
-      int cur = s;
-      for (int l = dep; l >= 1; --l) {
-        rows.anc[r * 4 + l - 1] = (int)(tb + cur);
-        cur = tr.parent[tb + cur];
-      }
-      for (int l = dep; l < 4; ++l) rows.anc[r * 4 + l] = 0;
-      rows.nanc[r] = dep;
+    const int e = (lo ? lo[u] : 0) + (r - off[u]);
+    const int s = idx ? idx[tb + e] : e;
+    const int dep = tr.depth[tb + s];
+    rows.user[r] = u;
+    rows.token[r] = tr.token[tb + s];
+    rows.pos[r] = P + dep - 1;
+    rows.slot[r] = (int)(tb + s);
+    rows.nctx[r] = P;
+    int cur = s;
+    for (int l = dep; l >= 1; --l) {
+      rows.anc[r * 4 + l - 1] = (int)(tb + cur);
+      cur = tr.parent[tb + cur];
     }
+    for (int l = dep; l < 4; ++l) rows.anc[r * 4 + l] = 0;
+    rows.nanc[r] = dep;
   }
 }
 
@@ -259,16 +291,21 @@ __global__ void __launch_bounds__(256) carry_copy_kernel(const int* src, const i
 }
 
 // Length of the prefix every user shares with user 0 (tokens equal at every
-// position before it), at most P.
-__global__ void common_prefix_kernel(const int* prefix, int B, int P, int* out) {
+// position before it), at most P.  Each thread keeps its smallest mismatch, so its
+// loads do not wait for each other.
+__global__ void __launch_bounds__(1024) common_prefix_kernel(const int* prefix, int B, int P, int* out) {
   __shared__ int len;
   if (threadIdx.x == 0) len = P;
   __syncthreads();
-  const int total = (B - 1) * P;
-  for (int i = threadIdx.x; i < total; i += blockDim.x) {
-    const int u = 1 + i / P, p = i % P;
-    if (prefix[u * P + p] != prefix[p]) atomicMin(&len, p);
+  int mine = P;
+  for (int p = threadIdx.x & 63; p < P; p += 64) {      // a wave per user, a lane per position
+    const int want = prefix[p];
+#pragma unroll 8
+    for (int u = 1 + (threadIdx.x >> 6); u < B; u += 16)
+      if (prefix[(size_t)u * P + p] != want) mine = min(mine, p);
   }
+  for (int o = 32; o > 0; o >>= 1) mine = min(mine, __shfl_xor(mine, o));
+  if ((threadIdx.x & 63) == 0) atomicMin(&len, mine);
   __syncthreads();
   if (threadIdx.x == 0) *out = len;
 }
@@ -539,11 +576,11 @@ void launch_append_beams(const StateDev& s, int B, int L, int* items, int* lens,
 void launch_tree_index(const TreeDev& tr, const TrieDev& trie, const StateDev& s, int B, int item_base, int codebook,
                        int L, int* err, hipStream_t st) {
   hipLaunchKernelGGL(tree_index_kernel, dim3(B), dim3(256), 0, st, tr, trie, s, item_base, codebook, L, err);
-  hipLaunchKernelGGL(find_beam_slots_kernel, dim3(B), dim3(64), 0, st, tr, s, L, err);
 }
 void launch_plan_tree(const TreeDev& tr, const int* lo, const int* hi, int B, int P, const Rows& rows, int* maxrows,
                       hipStream_t st, const int* idx) {
-  hipLaunchKernelGGL(plan_tree_rows_kernel, dim3(1), dim3(1024), 0, st, tr, lo, hi, idx, B, P, rows, maxrows);
+  const int blocks = (int)std::max<long>(1, std::min<long>(64, ((long)B * tr.max_nodes + 511) / 512));
+  hipLaunchKernelGGL(plan_tree_rows_kernel, dim3(blocks), dim3(256), 0, st, tr, lo, hi, idx, B, P, rows, maxrows);
 }
 void launch_carry_match(const TreeDev& tr, const StateDev& s, const uint32_t* prev_tpath, const int* prev_depth,
                         const int* prev_n, int* src, int* idx, int* cnt, int B, hipStream_t st) {
