@@ -18,56 +18,60 @@ namespace atspeed {
 // ---------------------------------------------------------------- tree kernels
 
 // Paths of the current beams Y_t (depths 1..t), deduplicated and level-ordered,
-// become the first nodes of each user's tree; beam_slot[k] is beam k's node.
-// The nodes are looked up while the tree is built, so their depth, path key
-// and trie node are mirrored in LDS (a lookup then costs no round trip to
-// memory): at most K <= 128 beams times t < L <= 4 levels of nodes.
-constexpr int kMaxPathNodes = kMaxSel * 3;
-__global__ void tree_from_beams_kernel(StateDev s, TreeDev tr, TrieDev trie, int item_base, int codebook, int L) {
-  __shared__ int dep_s[kMaxPathNodes], trie_s[kMaxPathNodes];
-  __shared__ uint32_t path_s[kMaxPathNodes];
-  const int u = blockIdx.x;
-  if (threadIdx.x != 0) return;
-  const int t = s.t[u];
-  const int nb = s.nb[u];
+// become the first nodes of each user's tree; beam_slot[k] is beam k's node.  A
+// thread per beam, level by level: a beam whose prefix no earlier beam has opens a
+// node, numbered in beam order (at most K <= 128 beams; a single thread walking the
+// lists took 17-33 us).
+__global__ void __launch_bounds__(kMaxSel)
+tree_from_beams_kernel(StateDev s, TreeDev tr, TrieDev trie, int item_base, int codebook, int L) {
+  __shared__ uint32_t path_s[kMaxSel];
+  __shared__ int node_s[kMaxSel], trie_s[kMaxSel], count[kMaxSel / 64];
+  const int u = blockIdx.x, k = threadIdx.x, lane = k & 63, wave = k >> 6;
+  const int t = s.t[u], nb = s.nb[u], K = s.K;
   int n = 0;
   const size_t tb = (size_t)u * tr.max_nodes;
-  const int K = s.K;
   if (t > 0 && t < L) {
+    if (k < nb) path_s[k] = s.path[u * K + k];
+    __syncthreads();
+    const uint32_t path = k < nb ? path_s[k] : 0u;
+    int parent = -1, ptrie = 0;                      // this beam's node of the level above
     for (int l = 1; l <= t; ++l) {
       const uint32_t mask = l == 4 ? 0xFFFFFFFFu : ~(0xFFFFFFFFu >> (8 * l));
-      for (int k = 0; k < nb; ++k) {
-        const uint32_t pre = s.path[u * K + k] & mask;
-        int found = -1;
-        for (int i = 0; i < n; ++i)
-          if (dep_s[i] == l && path_s[i] == pre) { found = i; break; }
-        if (found < 0) {
-          int parent = -1, ptrie = 0;
-          if (l > 1) {
-            const uint32_t pm = ~(0xFFFFFFFFu >> (8 * (l - 1)));
-            for (int i = 0; i < n; ++i)
-              if (dep_s[i] == l - 1 && path_s[i] == (pre & pm)) { parent = i; break; }
-            ptrie = parent >= 0 ? trie_s[parent] : 0;  // found: the prefix was added at level l - 1
-          }
-          const int code = path_code(pre, l - 1);
-          const int node = trie_child(trie, ptrie, code);
-          tr.token[tb + n] = item_base + codebook * (l - 1) + code;
-          tr.parent[tb + n] = parent;
-          tr.depth[tb + n] = l;
-          tr.q_score[tb + n] = 0.f;
-          tr.tpath[tb + n] = pre;
-          tr.ttrie[tb + n] = node;
-          dep_s[n] = l;
-          path_s[n] = pre;
-          trie_s[n] = node;
-          found = n++;
-        }
-        if (l == t) s.beam_slot[u * K + k] = found;
+      int first = k;                                 // the first beam with this prefix
+      if (k < nb)
+        for (int i = 0; i < k; ++i)
+          if ((path_s[i] & mask) == (path & mask)) { first = i; break; }
+      const bool opens = k < nb && first == k;
+      const unsigned long long b = __ballot(opens);
+      if (lane == 0) count[wave] = __popcll(b);
+      __syncthreads();
+      int slot = n + __popcll(b & ((1ull << lane) - 1ull));
+      for (int w = 0; w < wave; ++w) slot += count[w];
+      if (opens) {
+        const int code = path_code(path, l - 1), node = trie_child(trie, ptrie, code);
+        tr.token[tb + slot] = item_base + codebook * (l - 1) + code;
+        tr.parent[tb + slot] = parent;
+        tr.depth[tb + slot] = l;
+        tr.q_score[tb + slot] = 0.f;
+        tr.tpath[tb + slot] = path & mask;
+        tr.ttrie[tb + slot] = node;
+        node_s[k] = slot;
+        trie_s[k] = node;
       }
+      for (int w = 0; w < kMaxSel / 64; ++w) n += count[w];
+      __syncthreads();
+      if (k < nb) {
+        parent = node_s[first];
+        ptrie = trie_s[first];
+        if (l == t) s.beam_slot[u * K + k] = parent;
+      }
+      __syncthreads();                               // node_s and count are written again
     }
   }
-  tr.n_nodes[u] = n;
-  s.npath[u] = n;
+  if (k == 0) {
+    tr.n_nodes[u] = n;
+    s.npath[u] = n;
+  }
 }
 
 // Derived per-node data of a caller or draft tree: path key, trie node, ancestors;
@@ -75,13 +79,13 @@ __global__ void tree_from_beams_kernel(StateDev s, TreeDev tr, TrieDev trie, int
 // and the slots of Y_t's beams, each of which must be a node of depth t.
 // A node's walk is a chain of dependent lookups, so the tree's own arrays are
 // staged in LDS first (up to kStaged nodes), leaving one trie lookup a level.
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(1024)
 tree_index_kernel(TreeDev tr, TrieDev trie, StateDev s, int item_base, int codebook, int L, int* err) {
   constexpr int kStaged = 1024;
   __shared__ int nfwd, bad;
   __shared__ int dep_s[kStaged], par_s[kStaged], tok_s[kStaged];
   __shared__ uint32_t path_s[kStaged];
-  const int u = blockIdx.x, tid = threadIdx.x;
+  const int u = blockIdx.x, tid = threadIdx.x, nthr = blockDim.x;
   const size_t tb = (size_t)u * tr.max_nodes;
   const int t = s.t[u], n = t >= L ? 0 : tr.n_nodes[u];
   if (tid == 0) {
@@ -97,7 +101,7 @@ tree_index_kernel(TreeDev tr, TrieDev trie, StateDev s, int item_base, int codeb
   }
   const bool staged = n <= kStaged;
   if (staged)
-    for (int i = tid; i < n; i += 256) {
+    for (int i = tid; i < n; i += nthr) {
       dep_s[i] = tr.depth[tb + i];
       par_s[i] = tr.parent[tb + i];
       tok_s[i] = tr.token[tb + i];
@@ -106,7 +110,7 @@ tree_index_kernel(TreeDev tr, TrieDev trie, StateDev s, int item_base, int codeb
   auto depth = [&](int i) { return staged ? dep_s[i] : tr.depth[tb + i]; };
   auto parent = [&](int i) { return staged ? par_s[i] : tr.parent[tb + i]; };
   auto token = [&](int i) { return staged ? tok_s[i] : tr.token[tb + i]; };
-  for (int i = tid; i < n; i += 256) {
+  for (int i = tid; i < n; i += nthr) {
     int chain[4], dep = depth(i), cur = i, ok = dep >= 1 && dep <= L;
     for (int l = dep; ok && l >= 1; --l) {
       if (cur < 0 || cur > i || depth(cur) != l) { ok = 0; break; }
@@ -141,7 +145,7 @@ tree_index_kernel(TreeDev tr, TrieDev trie, StateDev s, int item_base, int codeb
   // validated ones keep those walks inside the tree and the tables.
   if (tid == 0) s.nfwd[u] = bad ? 0 : nfwd;
   if (t <= 0 || t >= L || bad) return;   // a malformed tree is reported as such
-  for (int k = tid; k < s.nb[u]; k += 256) {
+  for (int k = tid; k < s.nb[u]; k += nthr) {
     const uint32_t p = s.path[u * s.K + k];
     int found = -1;
     for (int i = 0; i < n; ++i)
@@ -568,14 +572,15 @@ __global__ void append_beams_kernel(StateDev s, int L, int* __restrict__ items, 
 // ---------------------------------------------------------------- launchers
 void launch_tree_from_beams(const StateDev& s, const TreeDev& tr, const TrieDev& trie, int B, int item_base,
                             int codebook, int L, hipStream_t st) {
-  hipLaunchKernelGGL(tree_from_beams_kernel, dim3(B), dim3(64), 0, st, s, tr, trie, item_base, codebook, L);
+  hipLaunchKernelGGL(tree_from_beams_kernel, dim3(B), dim3(kMaxSel), 0, st, s, tr, trie, item_base, codebook, L);
 }
 void launch_append_beams(const StateDev& s, int B, int L, int* items, int* lens, int* n, hipStream_t st) {
   hipLaunchKernelGGL(append_beams_kernel, dim3(B), dim3(64), 0, st, s, L, items, lens, n);
 }
 void launch_tree_index(const TreeDev& tr, const TrieDev& trie, const StateDev& s, int B, int item_base, int codebook,
                        int L, int* err, hipStream_t st) {
-  hipLaunchKernelGGL(tree_index_kernel, dim3(B), dim3(256), 0, st, tr, trie, s, item_base, codebook, L, err);
+  const int nthr = tr.max_nodes > 512 ? 1024 : tr.max_nodes > 256 ? 512 : 256;   // a thread per node: one walk's latency
+  hipLaunchKernelGGL(tree_index_kernel, dim3(B), dim3(nthr), 0, st, tr, trie, s, item_base, codebook, L, err);
 }
 void launch_plan_tree(const TreeDev& tr, const int* lo, const int* hi, int B, int P, const Rows& rows, int* maxrows,
                       hipStream_t st, const int* idx) {
