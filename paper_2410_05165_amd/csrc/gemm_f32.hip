@@ -13,12 +13,13 @@
 // partners.  The product therefore never goes through memory before its epilogue.
 //
 // Bound: fp32 MFMA rate (154 TFLOP/s in a large library product on this card) at
-// hundreds of rows, the serial chain of k-tiles at a few rows.  The kernel this
-// one replaced (64x64 tiles of vector FMAs, one LDS buffer, the product stored
-// and read back by an elementwise kernel) took, 960 rows at d 1024, f 2816:
-// q/k/v 163 us, gate/up 257, down 166 plus 10 per epilogue; this one 66 and
-// 120 us (92 TFLOP/s, the epilogue included).  At 60 rows of d 128, f 512 (one
-// user's tree) 10-64 us fell to 4.5-5.2.
+// hundreds of rows, the serial chain of k-tiles at a few rows, where a k-tile of a
+// 32x64 tile takes 0.36 us (0.52 with its fragments read after the barrier instead
+// of a k-tile ahead).  The kernel this one replaced (64x64 tiles of vector FMAs,
+// one LDS buffer, the product stored and read back by an elementwise kernel) took,
+// 960 rows at d 1024, f 2816: q/k/v 163 us, gate/up 257, down 166 plus 10 per
+// epilogue; this one 59, 100 and 57 (110 TFLOP/s, the epilogue included).  At 60
+// rows of d 128, f 512 (one user's tree) 10-64 us fell to 4-8.
 #include <algorithm>
 #include "common.h"
 #include "kernels.h"
@@ -156,46 +157,86 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_f32_kernel(F32Args a) {
 #pragma unroll
     for (int j = 0; j < 2 * TP; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int fr = lane & 15, kg = lane >> 4;
-
+  // Fragments of the next k-tile are read while this one's MFMAs issue, so a step
+  // costs its MFMA chain and one barrier.  Stage kt % NS is free once every wave
+  // holds k-tile kt's fragments, which the barrier of step kt tells.
+  const int ra = wave_m * TM * 16 + fr, rb = wave_n * 2 * TP * 16 + fr;   // rows 16 apart share their swizzle
+  int ao[2], bo[2];
 #pragma unroll
-  for (int s = 0; s < NS - 1; ++s)
-    if (s < nst) load(s);
-  for (int kt = 0; kt < nst; ++kt) {
-    // k-tile kt has landed when at most the loads of the NS - 2 tiles after it
-    // are outstanding; the barrier makes every wave's share visible, and tells
-    // that all have finished reading the stage that the next load overwrites
-    if (kt + NS - 2 < nst) wait_vm<(NA + NB) * (NS - 2)>();
-    else wait_vm<0>();
+  for (int kk = 0; kk < 2; ++kk) {
+    ao[kk] = ra * 128 + (((kk * 4 + kg) ^ swz32(ra)) << 4);
+    bo[kk] = BM * 128 + rb * 128 + (((kk * 4 + kg) ^ swz32(rb)) << 4);
+  }
+  f32x4_t af[2][2][TM], bf[2][2][2 * TP];
+  auto read = [&](int kt, auto Set) {
+    constexpr int set = decltype(Set)::value;
+    const unsigned char* st = lds + (kt % NS) * STAGE;
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i) af[set][kk][i] = *reinterpret_cast<const f32x4_t*>(st + ao[kk] + i * 2048);
+#pragma unroll
+      for (int j = 0; j < 2 * TP; ++j) bf[set][kk][j] = *reinterpret_cast<const f32x4_t*>(st + bo[kk] + j * 2048);
+    }
+  };
+  auto mma = [&](int kk, auto Set) {
+    constexpr int set = decltype(Set)::value;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < 2 * TP; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[set][kk][i][e], bf[set][kk][j][e], acc[i][j], 0, 0, 0);
+  };
+  auto barrier = [] {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (kt + NS - 1 < nst) load(kt + NS - 1);
-    const unsigned char* st = lds + (kt % NS) * STAGE;
-    const int nkk = half_tail && kt == nst - 1 ? 1 : 2;
-    auto step = [&](int kk) {
-      f32x4_t af[TM], bf[2 * TP];
-      const int ch = kk * 4 + kg;
+  };
+  typedef std::integral_constant<int, 0> I0;
 #pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int r = (wave_m * TM + i) * 16 + fr;
-        af[i] = *reinterpret_cast<const f32x4_t*>(st + r * 128 + ((ch ^ swz32(r)) << 4));
+  for (int s = 0; s < NS; ++s)
+    if (s < nst) load(s);
+  asm volatile("" ::: "memory");
+  if (nst >= NS) wait_vm<(NA + NB) * (NS - 1)>();
+  else wait_vm<0>();
+  barrier();
+  read(0, I0{});
+  int kt = 0;
+  // steps whose refill lies inside the k range, two at a time (one per register set)
+  for (; kt + 1 + NS < nst; kt += 2) {
+    static_for<2>([&](auto S) {
+      constexpr int cur = decltype(S)::value;
+      const int k = kt + cur;
+      asm volatile("" ::: "memory");
+      wait_vm<(NA + NB) * (NS - 2)>();
+      barrier();
+      read(k + 1, std::integral_constant<int, cur ^ 1>{});
+      __builtin_amdgcn_sched_barrier(0);
+      mma(0, S);
+      __builtin_amdgcn_sched_barrier(0);
+      load(k + NS);
+      __builtin_amdgcn_sched_barrier(0);
+      mma(1, S);
+    });
+  }
+  for (; kt < nst; kt += 2) {
+    static_for<2>([&](auto S) {
+      constexpr int cur = decltype(S)::value;
+      const int k = kt + cur;
+      if (k >= nst) return;
+      if (k + 1 < nst) {
+        asm volatile("" ::: "memory");
+        if (k + NS - 1 < nst) wait_vm<(NA + NB) * (NS - 2)>();
+        else wait_vm<0>();
+        barrier();
+        read(k + 1, std::integral_constant<int, cur ^ 1>{});
+        if (k + NS < nst) load(k + NS);
       }
-#pragma unroll
-      for (int j = 0; j < 2 * TP; ++j) {
-        const int r = (wave_n * 2 * TP + j) * 16 + fr;
-        bf[j] = *reinterpret_cast<const f32x4_t*>(st + BM * 128 + r * 128 + ((ch ^ swz32(r)) << 4));
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < 2 * TP; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(af[i][e], bf[j][e], acc[i][j], 0, 0, 0);
-    };
-    step(0);
-    if (nkk == 2) step(1);
-    asm volatile("" ::: "memory");
+      mma(0, S);
+      if (!half_tail || k + 1 < nst) mma(1, S);
+    });
   }
 
   // acc[i][j][r]: row 16 i + 4 kg + r, column 16 j + fr of the wave's tile
@@ -285,14 +326,19 @@ hipError_t gemm_f32(const GemmCall& g, hipStream_t st) {
   a.q = (float*)g.q; a.kdst = (float*)g.kdst; a.vdst = (float*)g.vdst; a.cosT = g.cosT; a.sinT = g.sinT;
   a.rows = g.rows; a.kv_mode = g.kv_mode; a.Pmax = g.Pmax; a.d = g.d; a.dh = g.dh; a.H = g.H;
   if (g.K % 16 != 0) return hipErrorInvalidValue;
-  // Large tiles read fewer LDS bytes per MFMA, but only pay once there are enough
-  // of them for every CU to hold work; below that 64x64 tiles (three workgroups
-  // fit a CU), and at a few rows 32x64 tiles, whose serial chain is the shortest.
+  // Tile by the time of a k-tile on the fullest CU, us, with n workgroups there:
+  // fitted at d 512 and 1,024, f 1,408 and 2,816, 10 to 1,900 rows (within 6% of the
+  // measured times).  A tile's own latency rules at few rows, where 32x64 has the
+  // shortest chain; with CUs full the fuller last round decides.
   const long M = std::max(1, g.Mmax);
-  auto tiles = [&](int bm, int bn) { return ((M + bm - 1) / bm) * ((g.N + bn - 1) / bn); };
-  if (tiles(128, 128) >= 384) return launch_f32<2, 2, 4, 2, 3>(g, a, st);
-  if (tiles(64, 64) >= 192) return launch_f32<2, 2, 2, 1, 3>(g, a, st);
-  return launch_f32<2, 2, 1, 1, 4>(g, a, st);
+  auto time = [&](int bm, int bn, float t0, float t1) {
+    const long n = (((M + bm - 1) / bm) * ((g.N + bn - 1) / bn) + 255) / 256;
+    return t0 + t1 * (float)n;
+  };
+  const float t32 = time(32, 64, 0.07f, 0.29f), t64 = time(64, 64, 0.08f, 0.53f), t128 = time(128, 64, 0.10f, 1.03f);
+  if (t32 <= t64 && t32 <= t128) return launch_f32<2, 2, 1, 1, 4>(g, a, st);
+  if (t64 <= t128) return launch_f32<2, 2, 2, 1, 3>(g, a, st);
+  return launch_f32<4, 2, 2, 1, 3>(g, a, st);
 }
 
 }  // namespace atspeed

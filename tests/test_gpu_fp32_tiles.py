@@ -20,8 +20,8 @@ CASES = {
     "dh32_half_tail": (96, 3, 16 * 21, 50, 1, 4),          # 16 rows, K 336 = 10.5 k-tiles
     "dh64_one_row_over": (128, 2, 16, 33, 1, 16),          # d_ffn 16: half a k-tile; 64 rows, then trees
     "dh128_ragged_rows": (256, 2, 16 * 5, 255, 3, 11),     # 132 rows, 1,020 head columns
-    "mid_tiles": (512, 8, 1408, 256, 9, 17),               # 64x64 tiles, 612 rows
-    "large_tiles": (1024, 8, 2816, 256, 12, 33),           # 128x128 tiles, 1,584 rows
+    "mid_tiles": (512, 8, 1408, 256, 9, 17),               # 612 rows: 32x64 and 64x64 tiles
+    "large_tiles": (1024, 8, 2816, 256, 12, 33),           # 1,584 rows: 64x64 and 128x64 tiles
     "three_key_tiles": (128, 1, 64, 64, 1, 48),            # 192 keys, d_head 128
 }
 
