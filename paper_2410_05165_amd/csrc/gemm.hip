@@ -1,10 +1,13 @@
 // Dense projections of the decoder block: Y[M, N] = X[M, K] · W[N, K]^T.
 //
 // bf16 path: MFMA v_mfma_f32_32x32x16_bf16 (fp32 accumulate), block tile
-// BM x BN x 64 fetched by direct global->LDS DMA into two LDS stages
-// (XOR-swizzled 16-byte chunks), or three to six for small row counts, wave
-// tile TM x TN blocks of 32x32, tile shape chosen by the row count.  Epilogues are
-// fused:
+// BM x BN x 64, wave tile TM x TN blocks of 32x32, operands through LDS in
+// XOR-swizzled 16-byte chunks.  Four pipelines, by the wave tile and the number
+// of LDS stages NS: k-tiles staged through registers (four waves, one per SIMD,
+// TM + TN >= 6), two stages fed by global->LDS DMA, three
+// to six stages fed by it, and the same with the next k-tile's fragments in
+// registers (wave tiles of at most 2x2).  The shape is the one that a fitted
+// model of the call's time prefers (gemm() below).  Epilogues are fused:
 //   QKV   rotary embedding on q and k, rounding to bf16, q to its row buffer,
 //         k/v scattered into the prefix cache or the tree KV buffer.  The tile's
 //         weight rows are interleaved (qkv_logical) so that a column's
@@ -798,9 +801,7 @@ gemm_bf16_kernel(const bf16_t* __restrict__ A, int lda, const int* __restrict__ 
 }
 
 // ------------------------------------------------------------------ launchers
-// Launch of one instantiation over the tiles of a call.  The widest tiles,
-// 256x256 of 8 waves (64x128 each, two waves per SIMD), let one wave's LDS and
-// barrier waits hide behind the other's MFMAs.
+// Launch of one instantiation over the tiles of a call.
 template <int BMAP, int EPI, int WMW, int WNW, int TMW, int TNW, int NS = 2>
 static hipError_t launch_bf16(const GemmCall& g, hipStream_t st) {
   using T = Tile<WMW, WNW, TMW, TNW>;
@@ -822,7 +823,6 @@ static hipError_t launch_bf16(const GemmCall& g, hipStream_t st) {
   return hipGetLastError();
 }
 
-#ifndef NO_DISPATCH
 // Tile shape of a call, by a model of its time: with n workgroups of a shape on
 // the fullest CU (at most `cap` at once, more take further rounds), a round of
 // nk k-tiles costs nk * max(lat, thr * n) + epi us and the launch t0 once.  lat
@@ -833,7 +833,7 @@ static hipError_t launch_bf16(const GemmCall& g, hipStream_t st) {
 // The constants are fitted to measurements on MI355X, weights cold in L2: d 256,
 // 768, 1,024, 2,048, 4,096 with f 1,024 to 11,008, 25 row counts from 10 to 4,800
 // (7,744 at d 4,096), about 17 shapes a call.  The model's picks are on average
-// within 0.2% (q/k/v), 0.4% (gate/up), 2.1% (o, down) and 1.3% (head) of the
+// within 0.3% (q/k/v, gate/up), 2.1% (o, down) and 1.3% (head) of the
 // fastest shape measured.  The rule before it (fixed row thresholds, and rounds
 // fitted at d 4,096 alone) was 14-21% off on the same grid: at 640 rows of
 // d 768, f 3,072 q/k/v took 13.3 instead of 9.2 us, gate/up 14.3 (10.9), o 7.2
@@ -927,6 +927,5 @@ hipError_t gemm(const GemmCall& g, hipStream_t st) {
     default: return pick_shape(kHeadShapes, M, g.N, g.K, 1).launch(g, st);
   }
 }
-#endif
 
 }  // namespace atspeed
