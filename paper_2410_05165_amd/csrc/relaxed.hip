@@ -95,20 +95,14 @@ __device__ inline void rank_parents(Parents& P) {
 // Extensions of the parents: path, parent index, canonical index, target and
 // draft cumulative scores (target only when the parent has a target row).
 __device__ inline int expand(const TrieDev& trie, const Parents& P, int lvl0, int codebook, CandBuf cb, SelShared& sh) {
-  if (threadIdx.x == 0) {
-    int acc = 0;
-    for (int i = 0; i < P.n; ++i) { sh.par_off[i] = acc; acc += trie.cnt[P.trie[i]]; }
-    sh.par_off[P.n] = acc;
-  }
-  __syncthreads();
-  const int n = sh.par_off[P.n];
+  const int n = list_parents(trie, P.n, P.trie, sh);
   for (int c = threadIdx.x; c < n; c += blockDim.x) {
     int lo = 0, hi = P.n - 1;
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
       if (sh.par_off[mid] <= c) lo = mid; else hi = mid - 1;
     }
-    const int child = trie.first[P.trie[lo]] + (c - sh.par_off[lo]);
+    const int child = sh.par_first[lo] + (c - sh.par_off[lo]);
     const int code = trie.code[child];
     const int col = codebook * lvl0 + code;
     cb.path[c] = path_with(P.path[lo], lvl0, code);
@@ -177,7 +171,7 @@ draft_relaxed_kernel(StateDev s, TreeDev tr, TrieDev trie, const float* lpq, con
                      int max_cand, RelaxArgs ra) {
   __shared__ Parents P;
   __shared__ SelShared sh;
-  __shared__ unsigned long long sel[2 * kMaxSel];
+  __shared__ unsigned long long sel[kMaxSel];
   __shared__ unsigned long long red64[4];
   __shared__ float red[4];
   __shared__ uint32_t win[kMaxSel];
@@ -291,7 +285,7 @@ verify_relaxed_kernel(StateDev s, TreeDev tr, TrieDev trie, const float* lpt, co
                       int* accepted_out, int* t_after_out) {
   __shared__ Parents P;
   __shared__ SelShared sh;
-  __shared__ unsigned long long sel[2 * kMaxSel];
+  __shared__ unsigned long long sel[kMaxSel];
   __shared__ unsigned long long red64[4];
   __shared__ float red[4];
   __shared__ uint32_t fin[kMaxSel];      // per-slot / per-draft outcome paths
