@@ -5,7 +5,8 @@
 // lexicographically.  A candidate's 64-bit selection key is
 //   (~orderkey(score) << 32) | pathkey
 // whose ascending order is: higher score first, then lexicographically smaller
-// sequence (the pinned tie-break).  Keys are unique because paths are.
+// sequence (the pinned tie-break).  Keys differ where paths do; the copies of a beam
+// or node that a caller gives twice have equal keys, and each is selected for itself.
 // TopK cuts the keys down to few more than K and ranks those, one workgroup per user.
 #include <algorithm>
 #include <climits>

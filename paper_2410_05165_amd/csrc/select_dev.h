@@ -184,8 +184,11 @@ __device__ inline void radix_smallest(const unsigned long long* keys, int n, int
   __syncthreads();
 }
 
-// The nsel smallest keys, ascending, into out[]; returns their number.  Bound by
-// latency (one workgroup, a few thousand keys at most): up to kList keys are ranked
+// The nsel smallest keys, ascending, into out[]; returns their number.  Equal keys
+// (a beam that the caller's state holds twice, a path that its tree holds twice) each
+// take a place of their own, so every one of the nsel entries is written; at most
+// kMaxPar copies of the nsel-th key and fewer than kMaxSel keys before it fit the list.
+// Bound by latency (one workgroup, a few thousand keys at most): up to kList keys are ranked
 // against each other at once.  More are first cut down to those whose score is at
 // least the nsel-th best of the threads' own best scores: nsel threads hold a key
 // that good, so none of the nsel best is lost, and about as many keys pass as are
@@ -194,7 +197,7 @@ __device__ inline void radix_smallest(const unsigned long long* keys, int n, int
 // cut them down.  Drafting 40 of 20 parents' or 40 drafted nodes' extensions for 16
 // users, level by level: 13.2 -> 9.0 us a level.
 __device__ inline int select_smallest(const unsigned long long* keys, int n, int nsel, unsigned long long* out, SelShared& sh) {
-  static_assert(kMaxSel <= kList, "every selection fits the list");
+  static_assert(kMaxSel + kMaxPar <= kList, "every selection fits the list");
   const int tid = threadIdx.x, nt = blockDim.x;
   if (nsel > n) nsel = n;
   int m = n;
@@ -236,7 +239,7 @@ __device__ inline int select_smallest(const unsigned long long* keys, int n, int
     const unsigned long long k = sh.list[i];
     int rank = 0;
 #pragma unroll 8
-    for (int j = 0; j < m; ++j) rank += sh.list[j] < k;
+    for (int j = 0; j < m; ++j) rank += sh.list[j] < k || (sh.list[j] == k && j < i);
     if (rank < nsel) out[rank] = k;
   }
   __syncthreads();
