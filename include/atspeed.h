@@ -106,7 +106,10 @@ typedef struct {
  *                 attn_norm, wq, wk, wv, wo ([d,d]), ffn_norm, w_gate, w_up ([f,d]), w_down ([d,f])
  *   final_norm    [d_model]
  *   lm_head_item  [L*codebook, d_model]: the output-head rows of the item tokens
- *                 (item_base .. item_base + L*codebook - 1); no other row is read. */
+ *                 (item_base .. item_base + L*codebook - 1); no other row is read.
+ * Alignment: tok_emb may start at any element.  The other matrices and the gains are
+ * read in 16-byte chunks and start at a multiple of 16 bytes, as every whole
+ * allocation does. */
 typedef struct {
   const void* tok_emb;
   const void* const* layers;

@@ -71,10 +71,17 @@ __device__ __forceinline__ void store4<bf16_t>(bf16_t* p, float a, float b, floa
   *reinterpret_cast<uint2*>(p) = w;
 }
 
-// Four consecutive stored values (aligned to their size) as floats.
-__device__ __forceinline__ float4 load4(const float* p) { return *reinterpret_cast<const float4*>(p); }
+// Four consecutive stored values as floats, in one load.  The embedding is the
+// caller's and may be a view at any element, so the load assumes an element's
+// alignment only (the device takes it whole at any address).
+typedef float f32x4_any_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_any_t __attribute__((ext_vector_type(2), aligned(2)));
+__device__ __forceinline__ float4 load4(const float* p) {
+  const f32x4_any_t v = *reinterpret_cast<const f32x4_any_t*>(p);
+  return make_float4(v.x, v.y, v.z, v.w);
+}
 __device__ __forceinline__ float4 load4(const bf16_t* p) {
-  const uint2 w = *reinterpret_cast<const uint2*>(p);
+  const u32x2_any_t w = *reinterpret_cast<const u32x2_any_t*>(p);
   return make_float4(__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
                      __uint_as_float(w.y & 0xffff0000u));
 }
