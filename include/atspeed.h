@@ -107,9 +107,10 @@ typedef struct {
  *   final_norm    [d_model]
  *   lm_head_item  [L*codebook, d_model]: the output-head rows of the item tokens
  *                 (item_base .. item_base + L*codebook - 1); no other row is read.
- * Alignment: tok_emb may start at any element.  The other matrices and the gains are
- * read in 16-byte chunks and start at a multiple of 16 bytes, as every whole
- * allocation does. */
+ * Alignment: tok_emb and fp32 matrices may start at any element (fp32 matrices are
+ * read faster from a multiple of 16 bytes).  bf16 matrices and the gains are read in
+ * 16-byte chunks and start at a multiple of 16 bytes, as every whole allocation
+ * does. */
 typedef struct {
   const void* tok_emb;
   const void* const* layers;

@@ -70,14 +70,23 @@ __device__ __forceinline__ void dma_rows(unsigned char* dst, const void* base, u
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory", "m0");
 }
 
-// At most N vector loads outstanding, and no LDS read.
+// A lane's 16 bytes of such an instruction by an ordinary load, for matrices that start
+// at any element: an element's alignment is all it assumes.
+typedef float f32x4_any_t __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ f32x4_any_t load_any(const void* base, uint32_t off) {
+  typedef const __attribute__((address_space(1))) unsigned char global_byte_t;
+  typedef const __attribute__((address_space(1))) f32x4_any_t global_f32x4_t;
+  return *(global_f32x4_t*)((global_byte_t*)base + off);
+}
+
+// At most N vector loads outstanding, and no LDS read or write.
 template <int N>
 __device__ __forceinline__ void wait_vm() {
   static_assert(N < 64, "vmcnt holds 6 bits");
   __builtin_amdgcn_s_waitcnt((N & 0xF) | (((N >> 4) & 3) << 14) | (0x7 << 4));
 }
 
-template <int WM, int WN, int TM, int TP, int NS, int BMAP>
+template <int WM, int WN, int TM, int TP, int NS, int BMAP, bool DMA>
 __global__ void __launch_bounds__(64 * WM * WN) gemm_f32_kernel(F32Args a) {
   constexpr int NW = WM * WN, BM = WM * TM * 16, BN = WN * TP * 32;
   constexpr int NA = BM / (8 * NW), NB = BN / (8 * NW);   // DMA instructions per wave and stage
@@ -142,13 +151,27 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_f32_kernel(F32Args a) {
     unsigned char* st = lds + (kt % NS) * STAGE;
     const uint32_t kb = (uint32_t)kt * 128u;
     const bool tail = half_tail && kt == nst - 1;
+    if constexpr (DMA) {
 #pragma unroll
-    for (int j = 0; j < NA; ++j)
-      dma_rows(st + (wave * NA + j) * 1024, abase, aoff[j] + kb - (tail && ((chi >> j) & 1) ? 64u : 0u));
+      for (int j = 0; j < NA; ++j)
+        dma_rows(st + (wave * NA + j) * 1024, abase, aoff[j] + kb - (tail && ((chi >> j) & 1) ? 64u : 0u));
 #pragma unroll
-    for (int j = 0; j < NB; ++j)
-      dma_rows(st + BM * 128 + (wave * NB + j) * 1024, bbase[j],
-               boff[j] + kb - (tail && ((chi >> (NA + j)) & 1) ? 64u : 0u));
+      for (int j = 0; j < NB; ++j)
+        dma_rows(st + BM * 128 + (wave * NB + j) * 1024, bbase[j],
+                 boff[j] + kb - (tail && ((chi >> (NA + j)) & 1) ? 64u : 0u));
+    } else {
+      f32x4_any_t va[NA], vb[NB];
+#pragma unroll
+      for (int j = 0; j < NA; ++j) va[j] = load_any(abase, aoff[j] + kb - (tail && ((chi >> j) & 1) ? 64u : 0u));
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        vb[j] = load_any(bbase[j], boff[j] + kb - (tail && ((chi >> (NA + j)) & 1) ? 64u : 0u));
+#pragma unroll
+      for (int j = 0; j < NA; ++j) *reinterpret_cast<f32x4_any_t*>(st + (wave * NA + j) * 1024 + lane * 16) = va[j];
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        *reinterpret_cast<f32x4_any_t*>(st + BM * 128 + (wave * NB + j) * 1024 + lane * 16) = vb[j];
+    }
   };
 
   f32x4_t acc[TM][2 * TP];
@@ -300,16 +323,16 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_f32_kernel(F32Args a) {
   }
 }
 
-template <int WM, int WN, int TM, int TP, int NS>
+template <int WM, int WN, int TM, int TP, int NS, bool DMA = true>
 hipError_t launch_f32(const GemmCall& g, const F32Args& in, hipStream_t st) {
   constexpr int BM = WM * TM * 16, BN = WN * TP * 32;
   F32Args a = in;
   a.Mt = std::max(1, (g.Mmax + BM - 1) / BM);
   const int Nt = (g.N + BN - 1) / BN;
   const dim3 grid(8 * ((a.Mt * Nt + 7) / 8)), block(64 * WM * WN);
-  if (g.kind == GEMM_QKV) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, TM, TP, NS, FB_QKV>), grid, block, 0, st, a);
-  else if (g.kind == GEMM_GU) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, TM, TP, NS, FB_GU>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, TM, TP, NS, FB_PLAIN>), grid, block, 0, st, a);
+  if (g.kind == GEMM_QKV) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, TM, TP, NS, FB_QKV, DMA>), grid, block, 0, st, a);
+  else if (g.kind == GEMM_GU) hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, TM, TP, NS, FB_GU, DMA>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((gemm_f32_kernel<WM, WN, TM, TP, NS, FB_PLAIN, DMA>), grid, block, 0, st, a);
   return hipGetLastError();
 }
 
@@ -326,6 +349,12 @@ hipError_t gemm_f32(const GemmCall& g, hipStream_t st) {
   a.q = (float*)g.q; a.kdst = (float*)g.kdst; a.vdst = (float*)g.vdst; a.cosT = g.cosT; a.sinT = g.sinT;
   a.rows = g.rows; a.kv_mode = g.kv_mode; a.Pmax = g.Pmax; a.d = g.d; a.dh = g.dh; a.H = g.H;
   if (g.K % 16 != 0) return hipErrorInvalidValue;
+  // The DMA takes 16-byte chunks; matrices that do not start at a multiple of 16 bytes
+  // (views into larger buffers) go through registers, which a k-tile's copy waits for:
+  // a forward of 930 rows of d 1024 in two layers 756 us instead of 651, 117 rows of d
+  // 128 185 instead of 142 (2,425 and 454 with vector FMAs).
+  if ((((uintptr_t)g.w0 | (uintptr_t)g.w1 | (uintptr_t)g.w2) & 15) != 0)
+    return launch_f32<2, 2, 2, 1, 3, false>(g, a, st);
   // Tile by the time of a k-tile on the fullest CU, us, with n workgroups there:
   // fitted at d 512 and 1,024, f 1,408 and 2,816, 10 to 1,900 rows (within 6% of the
   // measured times).  A tile's own latency rules at few rows, where 32x64 has the

@@ -1,5 +1,5 @@
-"""Weights that are views into larger buffers: the embedding may start at any element,
-and the results are bitwise those of an aligned copy."""
+"""Weights that are views into larger buffers: the embedding and fp32 matrices may start
+at any element, and the results are bitwise those of aligned copies."""
 import numpy as np
 import pytest
 
@@ -63,3 +63,18 @@ def test_embedding_at_any_element(dtype, d, heads, ffn, shift):
     got = _logits(_engine(w, tw, cat, lambda k: k == "tok_emb", shift), w, cat, pre)
     for a, b in zip(got, want):
         assert np.isfinite(b).all() and np.array_equal(a, b)
+
+
+# d_model, heads, d_ffn (an odd multiple of 16: the down projection's last k-tile is half filled), codebook
+@pytest.mark.parametrize("shift", [1, 2, 3])
+@pytest.mark.parametrize("d,heads,ffn,codebook", [(64, 2, 16, 7), (96, 3, 336, 50), (512, 4, 1040, 255)])
+def test_fp32_matrices_at_any_element(d, heads, ffn, codebook, shift):
+    w = _workload("fp32", d, heads, ffn, codebook)
+    cat = make_catalog(w)
+    pre = make_prefixes(w, cat)
+    tw = make_weights(w, "target")
+    want = _logits(_engine(w, tw, cat, lambda k: False, 0), w, cat, pre)
+    for names in ("wk", "w_up", "w_down", "lm_head", ""):           # one matrix of a call, and all of them
+        got = _logits(_engine(w, tw, cat, lambda k: names in k and "norm" not in k, shift), w, cat, pre)
+        for a, b in zip(got, want):
+            assert np.isfinite(b).all() and np.array_equal(a, b), names
