@@ -303,9 +303,11 @@ __global__ void __launch_bounds__(64 * WM * WN) gemm_f32_kernel(F32Args a) {
           const int pos = a.rows.pos[row];
           if (which < 2) {
             const float c = a.cosT[(size_t)pos * half + fi], s = a.sinT[(size_t)pos * half + fi];
-            const float y1 = x1 * c - x2 * s;
-            x2 = x2 * c + x1 * s;
-            x1 = y1;
+            // explicit fma of a rounded product: the same arithmetic in every tile shape
+            // (free contraction may differ between instantiations)
+            const float p1 = x2 * s, p2 = x1 * s;
+            x1 = __builtin_fmaf(x1, c, -p1);
+            x2 = __builtin_fmaf(x2, c, p2);
           }
           float* dst;
           if (which == 0) {

@@ -57,3 +57,39 @@ def test_fp32_logits(name):
         want = dec.path_logits(caches[u], [tokens_of(nodes[u][i], w) for i in inner])
         np.testing.assert_allclose(logits[u][inner], want, rtol=0, atol=1e-4)
     eng.close()
+
+
+# users of the batches; with one user they take every tile size in each kind of call
+BATCHES = {"mid_tiles": (2, 5, 9), "large_tiles": (3, 4, 7, 12)}
+
+
+@pytest.mark.parametrize("name", list(BATCHES))
+def test_rows_do_not_depend_on_their_batch(name):
+    """A user's logits are bitwise the same alone and in batches of any tile size."""
+    from paper_2410_05165_amd.binding import Engine
+    d, heads, ffn, codebook, users, hist = CASES[name]
+    dims = ModelDims(1, d, heads, ffn, 4 * codebook + 8, 8)
+    w = get_workload("tiny").with_(name=name, target=dims, draft=ModelDims(0, 0, 0, 0, 0, 0), codebook=codebook,
+                                   n_items=400, batch=users, hist_items=hist, prompt_len=0, K=16, N=32)
+    cat = make_catalog(w)
+    pre = make_prefixes(w, cat)
+    eng = Engine(w, make_weights(w, "target"), None, cat)
+    rng = np.random.default_rng(7)
+    trees = [[tuple(int(c) for c in cat[i]) for i in rng.permutation(len(cat))[:17]] for _ in range(users)]
+
+    def run(order):
+        n = len(order)
+        root = torch.full((n, w.n_item_tokens), float("nan"), dtype=torch.float32, device="cuda:0")
+        eng.atspeed_prefill(torch.from_numpy(np.ascontiguousarray(pre[order])).cuda(), root)
+        upload_tree(eng, [trees[u] for u in order], n)
+        logits = torch.zeros((n, eng.max_nodes, w.n_item_tokens), dtype=torch.float32, device="cuda:0")
+        eng.atspeed_tree_logits(logits)
+        return root.cpu().numpy(), logits.cpu().numpy()
+
+    root1, tree1 = run([users - 1])
+    assert np.isfinite(root1).all()
+    for n in BATCHES[name]:
+        root, tree = run(list(range(users - n, users)))    # the user's rows are the last ones
+        assert np.array_equal(root[-1], root1[0]), f"{name}: root logits among {n} users"
+        assert np.array_equal(tree[-1], tree1[0]), f"{name}: tree logits among {n} users"
+    eng.close()
