@@ -335,6 +335,8 @@ gemm_bf16_kernel(const bf16_t* __restrict__ A, int lda, const int* __restrict__ 
   constexpr int NLOADS = NA + NB, SLOTS = TM * TN;
   // chunk w goes after MFMA slot_of(w) of the 4 SLOTS from a barrier to the next
   constexpr auto slot_of = [](int w) constexpr { return w * 4 * SLOTS / NLOADS + 2; };
+  static_assert(slot_of(NLOADS - 1) < 4 * SLOTS, "every chunk of a k-tile has an MFMA to follow");
+  static_assert(TM + TN <= SLOTS, "every fragment of a k-step has an MFMA to follow");
   constexpr int EARLY = [=]() constexpr { int n = 0; while (n < NLOADS && slot_of(n) < SLOTS) ++n; return n; }();
   uint32_t off[NLOADS];
 #pragma unroll
