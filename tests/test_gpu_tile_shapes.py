@@ -25,6 +25,10 @@ CASES = {
     "d1024_dh64_p65": (1024, 16, 2816, 65, (2, 3, 4, 6, 12, 20, 31)),
     "d1280_dh128_p66": (1280, 10, 3200, 66, (2, 7, 18)),     # norm of a workgroup a row, the others a wave a row
     "d1024_dh128_p129": (1024, 8, 1408, 129, (2, 9, 25)),
+    # the shapes that only these widths and row counts take: the largest four-wave tiles of every projection
+    "d768_dh64_p64": (768, 12, 3072, 64, (21, 40)),
+    "d2048_dh128_p61": (2048, 16, 5504, 61, (6, 7, 9, 16, 22, 34, 51)),
+    "d4096_dh128_p61": (4096, 32, 4096, 61, (2, 3, 6, 9, 13)),
 }
 
 
