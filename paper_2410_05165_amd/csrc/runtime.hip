@@ -120,7 +120,11 @@ struct atspeed_ctx {
   int B = 0, P = 0;
   bool prefilled = false;
   bool drafted = false;
-  bool at_root = false;        // no user has left item level 0 since the prefill: the tree of paths is empty
+  // No user has left item level 0 since the prefill, so the tree of paths is empty
+  // and the draft does not forward it.  Set by the prefill alone; whatever writes
+  // state.t to another level clears it: advance_strict and advance_relaxed, through
+  // which every acceptance goes, and atspeed_set_state.
+  bool at_root = false;
   // tree-KV reuse (cfg.reuse_tree_kv): the target's per-layer tree K/V and its
   // log-probs by slot live in two buffer sets that alternate between verifies;
   // a verify of the decode loop takes the nodes the previous one already
@@ -881,19 +885,30 @@ atspeed_status atspeed_tree_logits(atspeed_ctx* c, float* logits) {
   return ATSPEED_OK;
 }
 
+// Acceptance: the only launches that move the users to another item level.
+static void advance_strict(atspeed_ctx& c, const float* lp, const float* root, unsigned long long* keys, int32_t* accepted,
+                           int32_t* t_after) {
+  c.at_root = false;
+  launch_verify_strict(c.state, c.tree, c.trie, lp, root, c.nitem, c.cfg.codebook, c.cfg.L, keys, c.max_cand, accepted,
+                       t_after, c.B, c.st);
+}
+static void advance_relaxed(atspeed_ctx& c, const float* lp, const float* root, const CandBuf& cand, const RelaxArgs& ra,
+                            int32_t* accepted, int32_t* t_after) {
+  c.at_root = false;
+  launch_verify_relaxed(c.state, c.tree, c.trie, lp, root, c.dft.lp, c.dft.root, c.nitem, c.cfg.codebook, c.cfg.L, cand,
+                        c.max_cand, ra, accepted, t_after, c.B, c.st);
+}
+
 static atspeed_status accept_on(atspeed_ctx* c, const float* lpt, const float* roott, int32_t* accepted,
                                 int32_t* t_after) {
-  const atspeed_config& cf = c->cfg;
-  c->at_root = false;
+  int32_t* acc = accepted ? accepted : c->acc_tmp;
+  int32_t* ta = t_after ? t_after : c->tafter_tmp;
   HIP_TRY(mark(*c, ATSPEED_K_SELECT));
-  if (cf.mode == ATSPEED_STRICT) {
-    launch_verify_strict(c->state, c->tree, c->trie, lpt, roott, c->nitem, cf.codebook, cf.L, c->keys, c->max_cand,
-                         accepted ? accepted : c->acc_tmp, t_after ? t_after : c->tafter_tmp, c->B, c->st);
+  if (c->cfg.mode == ATSPEED_STRICT) {
+    advance_strict(*c, lpt, roott, c->keys, acc, ta);
   } else {
     if (!c->drafted) return fail(ATSPEED_E_STATE, "relaxed verification needs the context's own draft of this step");
-    launch_verify_relaxed(c->state, c->tree, c->trie, lpt, roott, c->dft.lp, c->dft.root, c->nitem, cf.codebook, cf.L,
-                          c->cand, c->max_cand, c->relax, accepted ? accepted : c->acc_tmp,
-                          t_after ? t_after : c->tafter_tmp, c->B, c->st);
+    advance_relaxed(*c, lpt, roott, c->cand, c->relax, acc, ta);
   }
   HIP_TRY(hipGetLastError());
   HIP_TRY(mark(*c, -1));
@@ -968,18 +983,15 @@ atspeed_status atspeed_accept_noalloc(atspeed_ctx* c, const float* logits, const
   HIP_TRY(log_softmax_rows(root_logits, c->Mb, c->B, c->nitem, nullptr, root, nullptr, c->st));
   int* acc = accepted ? accepted : c->acc_tmp;
   int* ta = t_after ? t_after : c->tafter_tmp;
-  c->at_root = false;
   if (!relaxed) {
-    launch_verify_strict(c->state, c->tree, c->trie, lp, root, c->nitem, cf.codebook, cf.L, keys, c->max_cand, acc,
-                         ta, c->B, c->st);
+    advance_strict(*c, lp, root, keys, acc, ta);
   } else {
     RelaxArgs ra = c->relax;
     ra.keys = keys;
     CandBuf cb{reinterpret_cast<uint32_t*>(base + o_cand[0]), reinterpret_cast<int*>(base + o_cand[1]),
                reinterpret_cast<int*>(base + o_cand[2]), reinterpret_cast<float*>(base + o_cand[3]),
                reinterpret_cast<float*>(base + o_cand[4])};
-    launch_verify_relaxed(c->state, c->tree, c->trie, lp, root, c->dft.lp, c->dft.root, c->nitem, cf.codebook, cf.L,
-                          cb, c->max_cand, ra, acc, ta, c->B, c->st);
+    advance_relaxed(*c, lp, root, cb, ra, acc, ta);
   }
   HIP_TRY(hipGetLastError());
   HIP_TRY(hipStreamSynchronize(c->st));
@@ -1127,7 +1139,6 @@ atspeed_status atspeed_target_search(atspeed_ctx* c, int32_t B, int32_t P, const
   ST_TRY(prefill_impl(c, B, P, prefix, nullptr, false));
   const atspeed_config& cf = c->cfg;
   const int L = cf.L;
-  c->at_root = false;   // the searches advance the users' levels
   if (step_n) HIP_TRY(hipMemsetAsync(step_n, 0, sizeof(int) * B, c->st));
   for (int l = 0; l < L; ++l) {
     // the tree of the Y_t paths alone: the verify has no drafted level, so it
@@ -1135,8 +1146,7 @@ atspeed_status atspeed_target_search(atspeed_ctx* c, int32_t B, int32_t P, const
     launch_tree_from_beams(c->state, c->tree, c->trie, B, cf.target.item_base, cf.codebook, L, c->st);
     HIP_TRY(hipGetLastError());
     ST_TRY(tree_forward(*c, nullptr, true));
-    launch_verify_strict(c->state, c->tree, c->trie, c->tgt.lp, c->tgt.root, c->nitem, cf.codebook, L, c->keys,
-                         c->max_cand, c->acc_tmp, c->tafter_tmp, B, c->st);
+    advance_strict(*c, c->tgt.lp, c->tgt.root, c->keys, c->acc_tmp, c->tafter_tmp);
     HIP_TRY(hipGetLastError());
     if (step_items) {
       launch_append_beams(c->state, B, L, step_items, step_lens, step_n, c->st);
@@ -1258,22 +1268,20 @@ atspeed_status atspeed_mixed_search(atspeed_ctx* c, float lambda, int32_t B, int
   ST_TRY(prefill_impl(c, B, P, prefix, nullptr, true));
   const atspeed_config& cf = c->cfg;
   const int L = cf.L, path_rows = std::max(1, cf.K * (L - 1));
-  c->at_root = false;
   if (step_n) HIP_TRY(hipMemsetAsync(step_n, 0, sizeof(int) * B, c->st));
   for (int l = 0; l < L; ++l) {
     // the Y_t paths alone, through the target and the draft
     launch_tree_from_beams(c->state, c->tree, c->trie, B, cf.target.item_base, cf.codebook, L, c->st);
     HIP_TRY(hipGetLastError());
     ST_TRY(tree_forward(*c, nullptr, true));
-      launch_plan_tree(c->tree, nullptr, c->state.npath, B, c->P, c->rows, nullptr, c->st);
+    launch_plan_tree(c->tree, nullptr, c->state.npath, B, c->P, c->rows, nullptr, c->st);
     HIP_TRY(hipGetLastError());
     ST_TRY(forward(*c, c->dft, false, B * path_rows, path_rows, nullptr));
     // the mixture into the draft's rows, then the strict TopK of the next level
     if (l == 0) launch_mix_logprobs(c->dft.root, c->tgt.root, nullptr, B, 1, c->nitem, lambda, c->st);
     else launch_mix_logprobs(c->dft.lp, c->tgt.lp, c->state.npath, B, c->Tmax, c->nitem, lambda, c->st);
     HIP_TRY(hipGetLastError());
-    launch_verify_strict(c->state, c->tree, c->trie, c->dft.lp, c->dft.root, c->nitem, cf.codebook, L, c->keys,
-                         c->max_cand, c->acc_tmp, c->tafter_tmp, B, c->st);
+    advance_strict(*c, c->dft.lp, c->dft.root, c->keys, c->acc_tmp, c->tafter_tmp);
     HIP_TRY(hipGetLastError());
     if (step_items) {
       launch_append_beams(c->state, B, L, step_items, step_lens, step_n, c->st);
