@@ -4,9 +4,9 @@
 // BM x BN x 64, wave tile TM x TN blocks of 32x32, operands through LDS in
 // XOR-swizzled 16-byte chunks.  Four pipelines, by the wave tile and the number
 // of LDS stages NS: k-tiles staged through registers (four waves, one per SIMD,
-// TM + TN >= 6), two stages fed by global->LDS DMA, three
-// to six stages fed by it, and the same with the next k-tile's fragments in
-// registers (wave tiles of at most 2x2).  The shape is the one that a fitted
+// TM + TN >= 6), two stages fed by global->LDS DMA, three or four
+// stages fed by it, and three to six with the next k-tile's fragments in
+// registers (TM + TN <= 4).  The shape is the one that a fitted
 // model of the call's time prefers (gemm() below).  Epilogues are fused:
 //   QKV   rotary embedding on q and k, rounding to bf16, q to its row buffer,
 //         k/v scattered into the prefix cache or the tree KV buffer.  The tile's
@@ -46,7 +46,7 @@ struct EpiArgs {
   Rows rows;
   int kv_mode;       // 0 prefix cache [B][H][Pmax][dh], 1 tree [slot][d]
   int Pmax;
-  int d, dh, H;
+  int d, dh;
 };
 
 struct BArgs {
@@ -813,7 +813,7 @@ static hipError_t launch_bf16(const GemmCall& g, hipStream_t st) {
   e.part = EPI == EPI_RESID ? g.part : nullptr;
   e.q = (bf16_t*)g.q; e.kdst = (bf16_t*)g.kdst; e.vdst = (bf16_t*)g.vdst;
   e.ropeT = g.ropeT; e.rows = g.rows; e.kv_mode = g.kv_mode; e.Pmax = g.Pmax;
-  e.d = g.d; e.dh = g.dh; e.H = g.H;
+  e.d = g.d; e.dh = g.dh;
   const int kparts = e.part ? 2 : 1;
   // each k-range is an even number of k-tiles of 64 (two stages)
   if (g.K % (kparts * 128) != 0) return hipErrorInvalidValue;
@@ -830,7 +830,8 @@ static hipError_t launch_bf16(const GemmCall& g, hipStream_t st) {
 // nk k-tiles costs nk * max(lat, thr * n) + epi us and the launch t0 once.  lat
 // is a k-tile's own latency (barrier, LDS, MFMA chain), which few rows or few
 // columns are bound by: small tiles spread those calls over more CUs; thr is a
-// k-tile's share of a full CU, where large tiles move fewer bytes per MFMA.
+// k-tile's share of a full CU, where large tiles move fewer bytes per MFMA.  With
+// cap 1 only the larger of the two counts, and the other is whatever the fit left.
 //
 // The constants are fitted to measurements on MI355X, weights cold in L2: d 256,
 // 768, 1,024, 2,048, 4,096 with f 1,024 to 11,008, 25 row counts from 10 to 4,800

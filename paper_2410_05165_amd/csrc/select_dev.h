@@ -53,7 +53,6 @@ __device__ inline int trie_child(const TrieDev& t, int node, int code) {
 constexpr int kList = 256;    // keys that select_smallest ranks against each other
 struct SelShared {
   int hist[256];
-  int cum[4];
   unsigned long long prefix, mask;
   int need, done, count;
   int par_off[kMaxPar + 1], par_first[kMaxPar];

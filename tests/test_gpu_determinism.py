@@ -146,9 +146,9 @@ def test_few_row_tiles_are_batch_invariant():
 def test_tile_shapes_by_row_count_are_batch_invariant():
     """At the 7B widths: a user's prefill alone runs P target rows, inside the
     32-user batch P + 31 (P - shared) rows, so the two take different GEMM tile
-    shapes (narrow tiles to 64 rows, tall four-wave tiles at 65-128, 129-192 and
-    193-256, the cost model's wide tiles above).  Its root logits are bitwise the
-    same either way, for prefix lengths that put the lone user in each range."""
+    shapes (32x64 to 128x128 tiles at up to 256 rows, the large tiles in the batch).
+    Its root logits are bitwise the same either way, for prefix lengths that give
+    the lone user different tiles."""
     from paper_2410_05165_amd.binding import Engine
     from synth import get_workload, make_catalog, make_prefixes, make_weights
     w = get_workload("b7")
