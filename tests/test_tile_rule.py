@@ -1,6 +1,7 @@
 """The row counts of the GPU tests that compare a user's logits alone and in a batch
-reach every tile shape that the projections' rules can pick: the rules' own source
-text, compiled for the host, is asked which shape each call of those tests takes."""
+reach every tile shape that the projections' rules can pick, and the bf16 rule's
+picks are near the fastest shapes measured: the rules' own source text, compiled for
+the host, is asked which shape a call takes."""
 import os
 import re
 import subprocess
@@ -63,14 +64,19 @@ def _between(name, start, end):
     return src[a:src.index(end, a)]
 
 
-def _picks(tmp_path, source, calls):
+def _indices(tmp_path, source, calls):
+    """What the rule in ``source`` answers to each call (kind, M, N, K, parts of k)."""
     (tmp_path / "rule.cpp").write_text(source)
     exe = str(tmp_path / "rule")
     subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-o", exe, str(tmp_path / "rule.cpp")], check=True)
     text = "\n".join("%s %d %d %d %d" % c for c in calls)
     out = subprocess.run([exe], input=text, text=True, capture_output=True, check=True).stdout.split()
     assert len(out) == len(calls)
-    return {(c[0], int(i)) for c, i in zip(calls, out)}
+    return [int(i) for i in out]
+
+
+def _picks(tmp_path, source, calls):
+    return {(c[0], i) for c, i in zip(calls, _indices(tmp_path, source, calls))}
 
 
 def _block(M, d, ffn, split):
@@ -110,3 +116,38 @@ def test_fp32_batches_reach_every_tile(tmp_path):
             calls += _block(4 * hist * n, d, ffn, False)
     got = _picks(tmp_path, FP32_HOST % rule, calls)
     assert got == {(kind, t) for kind in "qgr" for t in tiles}
+
+
+def test_picks_are_near_the_fastest_measured_shape(tmp_path):
+    """The rule against the tracked measurements of the shapes: what its picks take
+    over the fastest measured shape, on average over the calls of a table."""
+    measured, head = {}, None
+    for line in open(os.path.join(os.path.dirname(os.path.dirname(CSRC)), "profiles", "gemm_shapes.csv")):
+        cells = line.strip().split(";")
+        if line.startswith("#"):
+            continue
+        if cells[0] == "projection":
+            head = cells[4:]
+        else:
+            times = {s: float(t) for s, t in zip(head, cells[4:]) if float(t) > 0}
+            measured[(cells[0], *map(int, cells[1:4]))] = times
+    rule = _between("gemm.hip", "namespace {\nconstexpr int kCUs", "hipError_t gemm(const GemmCall& g")
+    tables = {"qkv": ("q", "kQkvShapes"), "gu": ("g", "kGuShapes"), "o": ("r", "kResidShapes"), "down": ("r", "kResidShapes"),
+              "head": ("h", "kHeadShapes")}
+    calls, keys = [], []
+    for key in measured:
+        name, d, ffn, M = key
+        k = ffn if name == "down" else d
+        n = {"qkv": 3 * d, "gu": 2 * ffn, "head": 1024}.get(name, d)
+        calls.append((tables[name][0], M, n, k, 2 if name in ("o", "down") and k % 256 == 0 else 1))
+        keys.append(key)
+    index = _indices(tmp_path, BF16_HOST % rule, calls)
+    over = {}
+    for key, i in zip(keys, index):
+        kind, table = tables[key[0]]
+        rows = re.findall(r"launch_bf16<\w+, \w+, ([\d, ]+)>", _between("gemm.hip", f"const Shape {table}[]", "};"))
+        shape = rows[i].replace(" ", "")
+        over.setdefault(kind, []).append(np.log(measured[key][shape] / min(measured[key].values())))
+    mean = {kind: float(np.mean(v)) for kind, v in over.items()}
+    print(mean)
+    assert mean["q"] < 0.005 and mean["g"] < 0.005 and mean["r"] < 0.025 and mean["h"] < 0.015, mean
